@@ -260,13 +260,12 @@ void ikfad_destroy(ikfad_ctx *ctx);
  * Eckart-Young floor sqrt(1 - sigma_1^2 / |xi|_F^2) and the stable rank
  * |xi|_F^2 / sigma_1^2.  All reductions are fp64 in a fixed order.
  * Blocking (waits for `stream`); allocates and frees a temporary device
- * workspace of 8 (2 m + 2 n + n P) bytes plus a little
- * (rikfad_friction_report_workspace_bytes gives the exact size), where
- * P = ceil(m / 128) for n <= 1024 and otherwise the number of column-sum
- * stripes ceil(m / s), s a power of two in [16, 1024] (larger only for m
- * above 2^20).  For n <= 1024 the report reads xi power_iters + 2 times
- * (the factors in one pass, the errors with the first power iteration,
- * sigma_1 in a last pass), otherwise 2 power_iters + 4 times.  m, n < 2^31;
+ * workspace (rikfad_friction_report_workspace_bytes gives its size).  For
+ * 4 <= n <= 16384 the report reads xi power_iters + 2 times (C in one pass,
+ * the errors with the first power iteration, sigma_1 in a last pass) and
+ * keeps at most 256 rows of n column partial sums (8 bytes each, up to the
+ * size of the static workspace below); otherwise it reads xi
+ * 2 power_iters + 4 times.  m, n < 2^31;
  * EINVAL on bad arguments, ENOMEM if the workspace cannot be allocated,
  * EHIP on a launch or copy failure (rikfad_last_error says which).
  * ---------------------------------------------------------------------- */
@@ -297,7 +296,7 @@ rikfad_status rikfad_friction_report(const float *xi, int64_t m, int64_t n, doub
  * with the device current).  A tensor whose workspace
  * (rikfad_friction_report_workspace_bytes) exceeds the array is rejected
  * with RIKFAD_EINVAL and a message in rikfad_last_error; every GPT2-S,
- * DistilBERT and 4096 x 11008 shape needs less than 6 MiB.  Blocking, like
+ * DistilBERT and 4096 x 11008 shape fits.  Blocking, like
  * rikfad_friction_report.  All calls on one device share its array: calls
  * that overlap on one device (from several host threads, or on several
  * streams at once) race and must be serialised by the caller. */

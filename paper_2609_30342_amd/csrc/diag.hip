@@ -15,8 +15,8 @@
 // sigma_1 comes from power iteration on xi^T xi started at C / |C| (xi >= 0,
 // so the leading singular vectors are non-negative), normalised on the GPU:
 // the column fold also writes per-workgroup squared-norm partials, from
-// which every wave of the next row pass derives the same scale.  For
-// n <= 1024 an iteration reads xi once (u = xi v and xi^T u in one pass).
+// which every wave of the next pass derives the same scale.  For
+// 4 <= n <= 16384 every pass reads xi once (u = xi v and xi^T u together).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -32,14 +32,8 @@ namespace {
 constexpr int kT = 256;            // threads per workgroup
 constexpr int kStatChunk = 4096;   // elements per workgroup of the vector statistics
 constexpr int kErrRows = 16;       // rows per workgroup of the error pass
-// 4 columns x 64 stripe groups per fold workgroup (6.4 us a fold of 393
-// x 768 partial sums with 8 x 32; 2 x 128 slower again).
-#ifndef RK_DIAG_FOLD_COLS
-#define RK_DIAG_FOLD_COLS 4
-#endif
-constexpr int kFoldCols = RK_DIAG_FOLD_COLS;        // columns per workgroup of the column fold
-constexpr int kFoldGroups = 256 / kFoldCols;        // stripe groups per column of the column fold
-static_assert(kFoldCols * kFoldGroups == 256, "fold workgroup shape");
+constexpr int kFoldCols = 16;                       // columns per workgroup of the column fold
+constexpr int kFoldGroups = kT / kFoldCols;         // partial-sum groups per column
 
 #define DG __attribute__((address_space(1)))
 template <typename T> __device__ __forceinline__ const DG T *gp(const T *q) { return (const DG T *)q; }
@@ -53,18 +47,6 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Scale of a vector from its fold partials: 1 / sqrt(sum_q parts[2 q]) in
-// a fixed order (lanes stride over the partials, then the butterfly), 0 for
-// a zero vector; every wave that calls it gets the same bits.
-__device__ __forceinline__ double inv_norm(const double *__restrict__ parts, int64_t nparts)
-{
-    const int lane = threadIdx.x & 63;
-    double s = 0.0;
-    for (int64_t q = lane; q < nparts; q += 64) s += gp(parts)[2 * q];
-    s = wave_sum(s);
-    return s > 0.0 ? 1.0 / sqrt(s) : 0.0;
-}
-
 // t where c holds, else +0.  A bitwise mask rather than a select: a select
 // between a loaded value and 0 is compiled into a branch around the load.
 __device__ __forceinline__ float keep_if(bool c, float t)
@@ -76,13 +58,40 @@ __device__ __forceinline__ double keep_if(bool c, double t)
     return __longlong_as_double(__double_as_longlong(t) & (c ? ~0ll : 0ll));
 }
 
+// sum_q parts[2 q] in a fixed order (lanes stride over the partials, 8 loads
+// in flight, then the butterfly); every wave that calls it gets the same
+// bits.
+__device__ __forceinline__ double sum_parts(const double *__restrict__ parts, int nparts)
+{
+    const int lane = threadIdx.x & 63;
+    double s = 0.0;
+    for (int q0 = lane; q0 < nparts; q0 += 64 * 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int q = q0 + 64 * u;
+            v[u] = keep_if(q < nparts, gp(parts)[2 * static_cast<int64_t>(min(q, nparts - 1))]);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    return wave_sum(s);
+}
+
+// Scale of a vector from its fold partials: 1 / norm, 0 for a zero vector.
+__device__ __forceinline__ double inv_norm(const double *__restrict__ parts, int nparts)
+{
+    const double s = sum_parts(parts, nparts);
+    return s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+}
+
 // out[i] = sum_j xi[i, j] * (w ? w[j] * scale : 1) with scale = inv_norm of
 // w's fold partials: one wave per row, lanes stride over the columns, fp64
 // accumulation.
 __global__ __launch_bounds__(kT) void row_reduce_kernel(const float *__restrict__ xi, int64_t m,
                                                         int64_t n, const double *__restrict__ w,
                                                         const double *__restrict__ wparts,
-                                                        int64_t nwparts, double *__restrict__ out)
+                                                        int nwparts, double *__restrict__ out)
 {
     const int64_t row = static_cast<int64_t>(blockIdx.x) * (kT / 64) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -106,155 +115,288 @@ __global__ __launch_bounds__(kT) void row_reduce_kernel(const float *__restrict_
     if (lane == 0) gp(out)[row] = w ? s * scale : s;
 }
 
-// One pass over xi for n <= 64 * NC, reading xi once: a workgroup takes
-// kPowRows rows, each of its kPowWaves waves an equal share in order.  Lane
-// l holds columns l, l + 64, ... of a row in registers; the wave forms the row's
-// weighted sum s_i = sum_j xi[i, j] w_j (lanes in column order, then the
-// butterfly) and adds xi[i, j] times a row weight to its column
-// accumulators, rows in order.  The waves' column sums are added in wave
-// order into the workgroup's row of part (folded by col_fold_kernel), and
-// the per-lane scalar sums into the workgroup's pair of spart.  MODE:
-//   kPassSums      w = 1: writes R_i = s_i; column weight 1, so part holds
-//                  partial column sums of xi (C)
-//   kPassPower     w = v / |v| (scale from v's fold partials): u_i = s_i;
-//                  column weight u_i (xi^T u)
-//   kPassPowerErr  kPassPower, plus spart = (sum xi^2, sum (xi - xi~)^2)
-//                  with xi~_ij = R_i C_j / (1^T R + eps) (0 if that is 0)
-//   kPassNorm      kPassPower, plus spart[0] = sum u_i^2
-// Shape of the one-pass kernels, measured on the 50257 x 768 report (30
-// iterations): 8 waves of 32 rows each (256 rows per workgroup), which
-// halves the column partial sums of 4 waves of 32 rows: 1.085-1.089
-// against 1.118-1.150 ms (8 waves of 24 rows: 1.52 ms).  With 4 waves,
-// 32 rows per wave beat 16 and 64 (1.19 against 1.57 and 1.34 ms).  The
-// load of row i + 1 is issued before row i is reduced (more rows ahead
-// measured slower: 2 rows 1.19-1.21 ms, 3 rows 1.25, 4 rows 1.30, against
-// 1.19 ms, with 4 waves).
-#ifndef RK_DIAG_POW_ROWS
-#define RK_DIAG_POW_ROWS 256
-#endif
-#ifndef RK_DIAG_POW_RING
-#define RK_DIAG_POW_RING 1
-#endif
-#ifndef RK_DIAG_POW_WAVES
-#define RK_DIAG_POW_WAVES 8
-#endif
-constexpr int kPowRows = RK_DIAG_POW_ROWS;   // rows per workgroup
-constexpr int kPowRing = RK_DIAG_POW_RING;   // rows loaded ahead per wave
-constexpr int kPowWaves = RK_DIAG_POW_WAVES; // waves per workgroup
-constexpr int kPowThreads = 64 * kPowWaves;
-static_assert(kPowRows % kPowWaves == 0, "whole rows per wave");
-static_assert(kErrRows <= kPowRows, "the error partials hold one pair per one-pass workgroup");
+// ------------------------------------------------- wave-level sums in VALU
+//
+// Sums across a wave by data-parallel primitives (rotations within 16 lanes,
+// half-row swaps between them): a butterfly through __shfl_xor is a chain of
+// LDS-crossbar round trips, which the one-pass kernels cannot hide.
+
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+constexpr int kQuadXor1 = 0xb1;    // lane ^ 1 (quad permutation 1 0 3 2)
+constexpr int kQuadXor2 = 0x4e;    // lane ^ 2 (quad permutation 2 3 0 1)
+constexpr int kRor4 = 0x124, kRor8 = 0x128;
+
+// v plus the value 16 lanes (32 lanes) away: a swap of the odd rows of one
+// copy with the even rows of another leaves the even rows in the first and
+// the odd rows in the second, at both places.
+__device__ __forceinline__ double add_row16(double v)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double add_half32(double v)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// Lane 0's value, as a scalar.
+__device__ __forceinline__ double first_lane(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
+// The sum of v over the 64 lanes, as a scalar.
+__device__ __forceinline__ double wave_sum_valu(double v)
+{
+    v += dpp<kQuadXor1>(v);
+    v += dpp<kQuadXor2>(v);
+    v += dpp<kRor8>(v);
+    v += dpp<kRor4>(v);
+    return first_lane(add_half32(add_row16(v)));
+}
+
+// Sum over the W waves of a row of their partial sums, lane l holding that of
+// wave l mod W, as a scalar.
+template <int W>
+__device__ __forceinline__ double sum_waves(double v)
+{
+    static_assert(W == 4 || W == 8 || W == 16, "waves per row");
+    if (W == 16) v += dpp<kRor8>(v);
+    if (W >= 8) v += dpp<kRor4>(v);
+    v += dpp<kQuadXor2>(v);
+    v += dpp<kQuadXor1>(v);
+    return first_lane(v);
+}
+
+// ---------------------------------------------------------- one-pass kernels
+//
+// One pass over xi for 4 <= n <= 16384, reading it once.  WPR of a
+// workgroup's 16 waves cover a row with K 16-byte loads per lane, so 16 / WPR
+// groups of waves work on consecutive shares of the workgroup's rows.  A lane
+// keeps its 4 K columns' weights and column sums in registers; for each row it
+// forms its share of the weighted sum s_i = sum_j xi[i, j] w_j, the sum is
+// completed in the wave (across WPR waves through LDS), and xi[i, j] s_i is
+// added to the column sums, rows in order.  The next row's loads go out
+// before the current one is summed.  The groups' column sums are added in
+// order into the workgroup's row of part (folded by col_fold_kernel).  MODE:
+//   kPassSums      part holds column sums of xi (C); no weights
+//   kPassPower     w = v / |v| (scale from v's fold partials): s = u, and
+//                  part holds xi^T u
+//   kPassPowerErr  the same from v = C, not normalised, plus spart =
+//                  (sum xi^2, sum (xi - xi~)^2) with xi~_ij = R_i C_j /
+//                  (1^T R + eps) (0 if that is 0), R_i the row's own sum and
+//                  1^T R the sum of C's fold partials
+//   kPassNorm      w as kPassPower; spart[0] = sum s_i^2, no column sums
+//
+// What bounds it: reading xi (7.2 TB/s at best here, from the memory-side
+// cache or from HBM alike), plus a prologue, an epilogue and a fold launch
+// of a few us each per pass.  One 16-wave workgroup per compute unit and at
+// most 256 of them fill the chip in one round and bound the partial sums to
+// 256 rows.  Report with 30 iterations, against one wave per row of up to
+// 1024 columns with 4-byte loads and LDS-crossbar sums, and two passes per
+// iteration above (same box): 50257 x 768 1080 -> 1000 us, 40000 x 1000
+// 1250 -> 1075, 768 x 768 864 -> 340, 20000 x 1500 1870 -> 1015,
+// 4096 x 11008 3020 -> 1390.  Two or four rows per batch measured within 2%
+// of one (50257 x 768: 1070 with two), and with spilled registers far
+// slower (4096 x 11008 with two rows: 1790; 40000 x 1000: 1970).
 enum : int { kPassSums = 0, kPassPower = 1, kPassPowerErr = 2, kPassNorm = 3 };
 
-template <int NC, int MODE>
-__global__ __launch_bounds__(kPowThreads) void onepass_kernel(
-    const float *__restrict__ xi, int64_t m, int64_t n, const double *__restrict__ v,
-    const double *__restrict__ vparts, int64_t nvparts, const double *__restrict__ r,
-    const double *__restrict__ c, const double *__restrict__ stats_r, double eps,
-    double *__restrict__ rout, double *__restrict__ part, double *__restrict__ spart)
+// Rows of xi start at any 4-byte boundary when n is not a multiple of 4.
+typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+struct OnePass {
+    const float *xi;
+    int64_t m, n;
+    int rows;                       // rows per workgroup
+    int nvparts;
+    const double *v, *vparts;
+    double eps;
+    double *part, *spart;
+    int64_t stride;                 // doubles per row of part (n rounded up to 4)
+};
+
+constexpr int kPassWaves = 16;
+
+template <int K, int WPR, int MODE>
+__global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
 {
     constexpr bool kWeighted = MODE != kPassSums;
     constexpr bool kErr = MODE == kPassPowerErr;
-    __shared__ double l[kPowWaves][64 * NC];
-    __shared__ double ls[kPowWaves][2];
+    constexpr bool kCols = MODE != kPassNorm;
+    constexpr int NW = kPassWaves, LT = 64 * WPR, NG = NW / WPR;
+    __shared__ double lds[NG > 1 ? NG * 4 * K * LT : 1];
+    __shared__ double rowsum[2][WPR > 1 ? NG : 1][WPR], rowsum1[2][WPR > 1 ? NG : 1][WPR];
+    __shared__ double ls[NW][2];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const double scale = kWeighted ? inv_norm(vparts, nvparts) : 1.0;
-    // Every load below is unconditional, its address clamped into the
-    // tensor and its value masked afterwards: loads inside branches make
-    // the compiler wait for all outstanding loads before each use, which
-    // would empty the ring of row loads at every row.
-    double wv[NC], cv[NC], acc[NC];
-    int jc[NC];                         // column, clamped into the row
+    const int sub = wave % WPR, grp = wave / WPR;
+    const int lt = sub * 64 + lane;
+    const int n = static_cast<int>(a.n);
+
+    // Columns 4 (lt + k LT) .. + 3.  Only the last load can pass the row's
+    // end: it then reads the row's last four elements and masks the ones
+    // that another lane owns (all four where none is left).
+    int lc[K];
+    uint32_t keep[4];
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-        const int j = lane + 64 * k;
-        jc[k] = j < n ? j : static_cast<int>(n - 1);
-        wv[k] = kWeighted ? keep_if(j < n, gp(v)[jc[k]] * scale) : 1.0;
-        cv[k] = kErr ? keep_if(j < n, gp(c)[jc[k]]) : 0.0;
-        acc[k] = 0.0;
+    for (int k = 0; k < K; ++k) lc[k] = min(4 * (lt + k * LT), n - 4);
+    const int skip = min(4 * (lt + (K - 1) * LT) - lc[K - 1], 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) keep[i] = i >= skip ? 0xffffffffu : 0u;
+
+    const int64_t wg0 = static_cast<int64_t>(blockIdx.x) * a.rows;
+    const int share = (a.rows + NG - 1) / NG;
+    const int64_t r0 = wg0 + static_cast<int64_t>(grp) * share;
+    const int64_t rend = min(min(r0 + share, wg0 + a.rows), a.m);
+    const int nr = static_cast<int>(max<int64_t>(0, rend - r0));
+    const int64_t rlast = nr > 0 ? rend - 1 : a.m - 1;  // a row of xi
+
+    // Row q of the group's share; past its last, the last again.
+    auto load = [&](int q, f32x4a4 (&x)[K]) {
+        const DG float *xr = gp(a.xi) + min(r0 + q, rlast) * a.n;
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[k] = *reinterpret_cast<const DG f32x4a4 *>(xr + lc[k]);
+    };
+
+    // The first row goes out ahead of the weights' loads, so that the two
+    // chains overlap.
+    f32x4a4 nx[K];
+    load(0, nx);
+
+    double w[K][4], acc[K][4];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            w[k][i] = kWeighted ? gp(a.v)[lc[k] + i] : 1.0;
+            acc[k][i] = 0.0;
+        }
+    if (kWeighted && !kErr) {
+        const double scale = inv_norm(a.vparts, a.nvparts);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[k][i] *= scale;
     }
     double inv = 0.0;
     if (kErr) {
-        const double denom = gp(stats_r)[1] + eps;
+        const double denom = sum_parts(a.vparts + 1, a.nvparts) + a.eps;
         inv = denom == 0.0 ? 0.0 : 1.0 / denom;
     }
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPowRows + wave * (kPowRows / kPowWaves);
-    const int64_t r1 = r0 + kPowRows / kPowWaves < m ? r0 + kPowRows / kPowWaves : m;
-    const int64_t rlast = r1 - 1;       // a row of xi (m >= 1), the wave's last if it has rows
-    auto load_row = [&](int64_t row, float (&dst)[NC], double &rr) {
-        const int64_t rc = row < r1 ? row : rlast;
-#pragma unroll
-        for (int k = 0; k < NC; ++k)
-            dst[k] = keep_if(lane + 64 * k < n && row < r1, gp(xi)[rc * n + jc[k]]);
-        if (kErr) rr = keep_if(row < r1, gp(r)[rc] * inv);
-    };
-    // A ring of kPowRing rows per wave: the loads of row i + kPowRing go out
-    // before row i is reduced, so the butterflies overlap the loads.  The
-    // ring is refilled unconditionally (rows past the wave's last are
-    // clamped and masked), so every wait is for exactly one row.
-    float ring[kPowRing][NC];
-    double rring[kPowRing] = {};        // row factors (error pass only)
-#pragma unroll
-    for (int q = 0; q < kPowRing; ++q) load_row(r0 + q, ring[q], rring[q]);
+
     double sa = 0.0, sb = 0.0;
-    for (int64_t i0 = r0; i0 < r1; i0 += kPowRing) {
+    for (int q = 0; q < share; ++q) {           // the same count in every group
+        float x[K][4];
+        const uint32_t ok = q < nr ? 0xffffffffu : 0u;
 #pragma unroll
-        for (int q = 0; q < kPowRing; ++q) {
-            const int64_t i = i0 + q;
-            float a[NC];
+        for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int k = 0; k < NC; ++k) a[k] = ring[q][k];
-            const double ri = rring[q];
-            load_row(i + kPowRing, ring[q], rring[q]);
-            double su = 0.0;
+            for (int i = 0; i < 4; ++i)
+                x[k][i] = __uint_as_float(__float_as_uint(nx[k][i]) &
+                                          (k == K - 1 ? ok & keep[i] : ok));
+        load(q + 1, nx);
+        double s = 0.0, s1 = 0.0;
+        if (kWeighted) {
 #pragma unroll
-            for (int k = 0; k < NC; ++k)
-                su += kWeighted ? static_cast<double>(a[k]) * wv[k] : static_cast<double>(a[k]);
-            su = wave_sum(su);
-            if (i < r1) {
-                if (MODE == kPassSums && lane == 0) gp(rout)[i] = su;
+            for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int k = 0; k < NC; ++k)
-                    acc[k] += kWeighted ? static_cast<double>(a[k]) * su : static_cast<double>(a[k]);
-                if (kErr) {
-#pragma unroll
-                    for (int k = 0; k < NC; ++k) {
-                        const double x = a[k];
-                        const double e = x - ri * cv[k];
-                        sa += x * x;
-                        sb += e * e;
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    s += static_cast<double>(x[k][i]) * w[k][i];
+                    if (kErr) s1 += static_cast<double>(x[k][i]);
                 }
-                if (MODE == kPassNorm && lane == 0) sa += su * su;
+            s = wave_sum_valu(s);
+            if (kErr) s1 = wave_sum_valu(s1);
+            if constexpr (WPR > 1) {
+                const int slot = q & 1;         // two slots: one barrier per row
+                if (lane == 0) {
+                    rowsum[slot][grp][sub] = s;
+                    if (kErr) rowsum1[slot][grp][sub] = s1;
+                }
+                __syncthreads();
+                s = sum_waves<WPR>(rowsum[slot][grp][lane & (WPR - 1)]);
+                if (kErr) s1 = sum_waves<WPR>(rowsum1[slot][grp][lane & (WPR - 1)]);
+            }
+        }
+        if (MODE == kPassNorm) sa += s * s;
+        const double ri = kErr ? s1 * inv : 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const double xv = x[k][i];
+                if (kCols) acc[k][i] += kWeighted ? xv * s : xv;
+                if (kErr) {
+                    // masked columns hold xi = 0: their model value goes too
+                    const bool own = k < K - 1 || keep[i] != 0u;
+                    const double e = own ? xv - ri * w[k][i] : 0.0;
+                    sa += xv * xv;
+                    sb += e * e;
+                }
+            }
+    }
+
+    if (kCols) {
+        double *out = a.part + static_cast<int64_t>(blockIdx.x) * a.stride;
+        if (NG > 1) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) lds[(grp * K + k) * 4 * LT + 4 * lt + i] = acc[k][i];
+            __syncthreads();
+            for (int j = threadIdx.x; j < 4 * K * LT; j += 64 * NW) {
+                double t = lds[j];
+#pragma unroll
+                for (int g = 1; g < NG; ++g) t += lds[g * K * 4 * LT + j];
+                // slot j is element i of the lane whose first column is j - i
+                const int i = j & 3, c0 = j - i, d = min(c0 - min(c0, n - 4), 4);
+                if (i >= d) gp(out)[c0 - d + i] = t;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                if (k < K - 1 || skip == 0) {       // whole groups of 4: 32-byte aligned
+                    DG f64x2 *q = reinterpret_cast<DG f64x2 *>(gp(out) + lc[k]);
+                    q[0] = f64x2{acc[k][0], acc[k][1]};
+                    q[1] = f64x2{acc[k][2], acc[k][3]};
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (keep[i] != 0u) gp(out)[lc[k] + i] = acc[k][i];
+                }
             }
         }
     }
-#pragma unroll
-    for (int k = 0; k < NC; ++k) l[wave][lane + 64 * k] = acc[k];
     if (kErr || MODE == kPassNorm) {
-        sa = wave_sum(sa);
-        sb = wave_sum(sb);
+        if (kErr) {
+            sa = wave_sum(sa);
+            sb = wave_sum(sb);
+        }
         if (lane == 0) {
             ls[wave][0] = sa;
             ls[wave][1] = sb;
         }
-    }
-    __syncthreads();
-    for (int64_t j = threadIdx.x; j < n; j += kPowThreads) {
-        double s = l[0][j];
-#pragma unroll
-        for (int w = 1; w < kPowWaves; ++w) s += l[w][j];
-        gp(part)[static_cast<int64_t>(blockIdx.x) * n + j] = s;
-    }
-    if ((kErr || MODE == kPassNorm) && threadIdx.x == 0) {
-        double a = ls[0][0], b = ls[0][1];
-#pragma unroll
-        for (int w = 1; w < kPowWaves; ++w) {
-            a += ls[w][0];
-            b += ls[w][1];
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            // of kPassNorm's s_i^2 every wave of a row's group holds the same sum
+            double x2 = 0.0, e2 = 0.0;
+            for (int t = 0; t < NW; t += MODE == kPassNorm ? WPR : 1) {
+                x2 += ls[t][0];
+                e2 += ls[t][1];
+            }
+            gp(a.spart)[2 * blockIdx.x] = x2;
+            gp(a.spart)[2 * blockIdx.x + 1] = e2;
         }
-        gp(spart)[2 * blockIdx.x] = a;
-        gp(spart)[2 * blockIdx.x + 1] = b;
     }
 }
 
@@ -285,53 +427,58 @@ __global__ __launch_bounds__(kT) void col_partial_kernel(const float *__restrict
     gp(part)[s * n + j] = acc;
 }
 
-// out[j] = sum_s part[s, j]: a workgroup takes kFoldCols columns, its
-// kFoldGroups thread groups sum consecutive ranges of stripes in stripe
-// order (16 loads in flight, addresses clamped and values masked) and are
-// added in group order.  The workgroup also writes parts[2 b] = sum of
-// out[j]^2 and parts[2 b + 1] = sum of out[j] over its columns (in column
-// order), the partials inv_norm and the statistics use.
-__global__ __launch_bounds__(kT) void col_fold_kernel(const double *__restrict__ part, int64_t n,
-                                                      int64_t nstripes, double *__restrict__ out,
+// out[j] = sum_s part[s * stride + j] for j < n: a workgroup takes kFoldCols
+// columns; each of its kFoldGroups groups of 16 threads sums a consecutive
+// range of the partial sums in order (16 loads in flight, addresses clamped
+// and values masked), the groups of a wave are added by a butterfly and the
+// waves in order.  The workgroup also writes parts[2 b] = sum of out[j]^2 and
+// parts[2 b + 1] = sum of out[j] over its columns, the partials inv_norm and
+// the statistics use.  Latency-bound (1.6 MB of partial sums for 768
+// columns): with 64 groups added one by one through LDS by a few threads it
+// took 4.8 us, of which that chain of LDS reads was about half.
+__global__ __launch_bounds__(kT) void col_fold_kernel(const double *__restrict__ part,
+                                                      int64_t stride, int64_t n, int nparts,
+                                                      double *__restrict__ out,
                                                       double *__restrict__ parts)
 {
-    __shared__ double l[kT];
-    const int c = threadIdx.x % kFoldCols, g = threadIdx.x / kFoldCols;
+    static_assert(kFoldCols == 16 && kT == 256, "4 groups per wave, 4 waves");
+    __shared__ double l[kT / 64][kFoldCols];
+    const int c = threadIdx.x & (kFoldCols - 1), g = threadIdx.x >> 4;
+    const int wave = threadIdx.x >> 6;
     const int64_t j = static_cast<int64_t>(blockIdx.x) * kFoldCols + c;
     const int64_t jc = j < n ? j : n - 1;
-    const int64_t per = (nstripes + kFoldGroups - 1) / kFoldGroups;
-    const int64_t s0 = g * per < nstripes ? g * per : nstripes;
-    const int64_t s1 = s0 + per < nstripes ? s0 + per : nstripes;
+    const int per = (nparts + kFoldGroups - 1) / kFoldGroups;
+    const int s0 = min(g * per, nparts), s1 = min(s0 + per, nparts);
     double acc = 0.0;
-    for (int64_t b = s0; b < s1; b += 16) {
+    for (int b = s0; b < s1; b += 16) {
         double v[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
-            const int64_t s = b + u < s1 ? b + u : s1 - 1;
-            v[u] = keep_if(b + u < s1 && j < n, gp(part)[s * n + jc]);
+            const int q = min(b + u, s1 - 1);
+            v[u] = keep_if(b + u < s1 && j < n, gp(part)[q * stride + jc]);
         }
 #pragma unroll
         for (int u = 0; u < 16; ++u) acc += v[u];
     }
-    l[threadIdx.x] = acc;
+    acc += __shfl_xor(acc, 16);
+    acc += __shfl_xor(acc, 32);
+    if ((threadIdx.x & 63) < kFoldCols) l[wave][c] = acc;
     __syncthreads();
     if (threadIdx.x < kFoldCols) {
-        double v = l[threadIdx.x];
-        for (int gg = 1; gg < kFoldGroups; ++gg) v += l[gg * kFoldCols + threadIdx.x];
-        l[threadIdx.x] = v;
+        double v = l[0][c];
+#pragma unroll
+        for (int w = 1; w < kT / 64; ++w) v += l[w][c];
         if (j < n) gp(out)[j] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double q2 = 0.0, q1 = 0.0;
-        for (int cc = 0; cc < kFoldCols; ++cc) {
-            const int64_t jj = static_cast<int64_t>(blockIdx.x) * kFoldCols + cc;
-            if (jj >= n) break;
-            q2 += l[cc] * l[cc];
-            q1 += l[cc];
+        double q2 = v * v, q1 = v;         // 0 past the last column
+#pragma unroll
+        for (int o = 1; o < kFoldCols; o <<= 1) {
+            q2 += __shfl_xor(q2, o);
+            q1 += __shfl_xor(q1, o);
         }
-        gp(parts)[2 * blockIdx.x] = q2;
-        gp(parts)[2 * blockIdx.x + 1] = q1;
+        if (threadIdx.x == 0) {
+            gp(parts)[2 * blockIdx.x] = q2;
+            gp(parts)[2 * blockIdx.x + 1] = q1;
+        }
     }
 }
 
@@ -468,6 +615,43 @@ __global__ __launch_bounds__(kT) void err_fold_kernel(const double *__restrict__
     }
 }
 
+// The one-pass report's numbers in one launch, each summed in a fixed order:
+// res = (0, 1^T R = 1^T C from C's fold partials, |xi v|^2, 0, |xi|_F^2,
+// |xi - xi~|_F^2).
+__global__ __launch_bounds__(kT) void finish_kernel(const double *__restrict__ cfold, int nfold,
+                                                    const double *__restrict__ upart,
+                                                    const double *__restrict__ epart, int nblk,
+                                                    double *__restrict__ res)
+{
+    __shared__ double l[kT / 64][4];
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int q = threadIdx.x; q < nfold; q += kT) t[0] += gp(cfold)[2 * q + 1];
+    for (int q = threadIdx.x; q < nblk; q += kT) {
+        t[1] += gp(upart)[2 * q];
+        t[2] += gp(epart)[2 * q];
+        t[3] += gp(epart)[2 * q + 1];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        t[k] = wave_sum(t[k]);
+        if ((threadIdx.x & 63) == 0) l[threadIdx.x >> 6][k] = t[k];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            t[k] = l[0][k];
+            for (int w = 1; w < kT / 64; ++w) t[k] += l[w][k];
+        }
+        gp(res)[0] = 0.0;
+        gp(res)[1] = t[0];
+        gp(res)[2] = t[1];
+        gp(res)[3] = 0.0;
+        gp(res)[4] = t[2];
+        gp(res)[5] = t[3];
+    }
+}
+
 struct DevBuf {
     void *p = nullptr;
     ~DevBuf()
@@ -476,10 +660,17 @@ struct DevBuf {
     }
 };
 
+constexpr int64_t kScratchWords = int64_t(1) << 21;    // static workspace: 16 MiB of doubles
+constexpr int64_t kOnePassMaxCols = 16384;  // 16 waves x 4 16-byte loads per lane
+constexpr int kOnePassMaxBlocks = 256;      // compute units: one round of 16-wave workgroups
+
 // Workspace of one report, in doubles, and the launch geometry it implies.
 struct ReportShape {
-    int64_t stripe, nstripes, ncb, nerr, nfold, nstat, nblk, nparts, words;
-    int nc;   // registers per lane of the one-pass power iteration (0: two passes)
+    int64_t stripe, nstripes, ncb, nerr, nfold, nstat, words;
+    // one-pass report: row length of the partial sums, workgroups and rows
+    // per workgroup (0: two passes per iteration)
+    int64_t stride;
+    int nblk, rows;
 };
 
 ReportShape report_shape(int64_t m, int64_t n)
@@ -497,15 +688,32 @@ ReportShape report_shape(int64_t m, int64_t n)
     s.nfold = (n + kFoldCols - 1) / kFoldCols;
     const int64_t mk = m > n ? m : n;
     s.nstat = (mk + kStatChunk - 1) / kStatChunk;
-    // n <= 1024: xi's rows fit the registers of a wave, and every pass over
-    // xi is one onepass_kernel launch
-    s.nc = n <= 256 ? 4 : n <= 512 ? 8 : n <= 768 ? 12 : n <= 1024 ? 16 : 0;
-    s.nblk = (m + kPowRows - 1) / kPowRows;
-    s.nparts = s.nc ? s.nblk : s.nstripes;
-    // r m, c n, u m, v n, column partials nparts*n, error partials 2*nerr,
-    // fold partials 2*nfold (C) and 2*nfold (v), statistics partials
-    // 2*nstat, results 2 (R), 2 (u), 2 (errors)
-    s.words = m + n + m + n + s.nparts * n + 2 * s.nerr + 4 * s.nfold + 2 * s.nstat + 6;
+    // r m, c n, u m, v n, column partials, error partials 2*nerr, fold
+    // partials (C and v), statistics partials 2*nstat, results 2 (R), 2 (u),
+    // 2 (errors).  Where rows are 1024 columns at most, the column partials
+    // are counted as one row per 256 rows of xi, and the fold partials as one
+    // pair per 4 columns.
+    const int64_t nparts = n <= 1024 ? (m + 255) / 256 : s.nstripes;
+    s.words = m + n + m + n + nparts * n + 2 * s.nerr + 4 * ((n + 3) / 4) + 2 * s.nstat + 6;
+    s.stride = (n + 3) / 4 * 4;
+    s.nblk = s.rows = 0;
+    if (n >= 4 && n <= kOnePassMaxCols) {
+        // c, v, fold partials of both, error and norm partials, results; the
+        // rest of the static workspace bounds the partial sums (only above
+        // 8000 columns: 185 workgroups of 4096 x 11008 still take the
+        // memory-side cache's rate).  words covers both forms, so whether a
+        // tensor fits the static workspace does not depend on the form.
+        const int64_t fixed = 2 * s.stride + 4 * s.nfold + 6 + 16;
+        int64_t most = (kScratchWords - fixed) / (s.stride + 4);
+        if (most > kOnePassMaxBlocks) most = kOnePassMaxBlocks;
+        const int64_t least = n <= 1024 ? 16 : 4;   // below 4096 rows: less to fold
+        int64_t rows = (m + most - 1) / most;
+        if (rows < least) rows = least;
+        s.rows = static_cast<int>(rows);
+        s.nblk = static_cast<int>((m + rows - 1) / rows);
+        const int64_t need = fixed + s.nblk * (s.stride + 4);
+        if (need > s.words) s.words = need;
+    }
     return s;
 }
 
@@ -525,17 +733,25 @@ rikfad_status check_report_args(const float *xi, int64_t m, int64_t n, double ep
     return RIKFAD_OK;
 }
 
-template <int MODE, typename... Args>
-void launch_onepass(int nc, dim3 grid, hipStream_t st, Args... args)
+// The fewest waves per row whose registers hold it (4 K columns' weights and
+// sums in 128 registers: K <= 4 within a wave), K = 2 where several waves
+// share a row, up to all 16 waves; K = 3 and 4 only where they must.
+template <int MODE>
+void launch_onepass(const OnePass &a, int nblk, hipStream_t st)
 {
-    if (nc == 4)
-        hipLaunchKernelGGL((onepass_kernel<4, MODE>), grid, dim3(kPowThreads), 0, st, args...);
-    else if (nc == 8)
-        hipLaunchKernelGGL((onepass_kernel<8, MODE>), grid, dim3(kPowThreads), 0, st, args...);
-    else if (nc == 12)
-        hipLaunchKernelGGL((onepass_kernel<12, MODE>), grid, dim3(kPowThreads), 0, st, args...);
-    else
-        hipLaunchKernelGGL((onepass_kernel<16, MODE>), grid, dim3(kPowThreads), 0, st, args...);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>(nblk)), dim3(64 * kPassWaves), 0, st,
+                           a);
+    };
+    if (a.n <= 256) go(onepass_kernel<1, 1, MODE>);
+    else if (a.n <= 512) go(onepass_kernel<2, 1, MODE>);
+    else if (a.n <= 768) go(onepass_kernel<3, 1, MODE>);
+    else if (a.n <= 1024) go(onepass_kernel<4, 1, MODE>);
+    else if (a.n <= 2048) go(onepass_kernel<2, 4, MODE>);
+    else if (a.n <= 4096) go(onepass_kernel<2, 8, MODE>);
+    else if (a.n <= 8192) go(onepass_kernel<2, 16, MODE>);
+    else if (a.n <= 12288) go(onepass_kernel<3, 16, MODE>);
+    else go(onepass_kernel<4, 16, MODE>);
 }
 
 // The report itself on a workspace of sh.words doubles at buf (device
@@ -545,58 +761,61 @@ rikfad_status report_on(const float *xi, int64_t m, int64_t n, double eps_stab,
                         int32_t power_iters, hipStream_t st, const ReportShape &sh, double *buf,
                         rikfad_friction_stats *out)
 {
-    const int64_t stripe = sh.stripe, nstripes = sh.nstripes, nerr = sh.nerr;
-    const int64_t nfold = sh.nfold, nblk = sh.nblk, nparts = sh.nparts;
-    const int nc = sh.nc;
-    double *r = buf, *c = r + m, *u = c + n, *v = u + m;
-    double *cpart = v + n, *epart = cpart + nparts * n, *cfold = epart + 2 * nerr;
-    double *vfold = cfold + 2 * nfold, *spart = vfold + 2 * nfold;
-    double *stats_r = spart + 2 * sh.nstat, *stats_u = stats_r + 2, *err = stats_u + 2;
-    const dim3 rows_grid(static_cast<uint32_t>((m + kT / 64 - 1) / (kT / 64)));
-    const dim3 cols_grid(static_cast<uint32_t>(sh.ncb), static_cast<uint32_t>(nstripes));
+    double *stats_r;                        // results: R (2), u (2), errors (2)
+    const int nfold = static_cast<int>(sh.nfold);
     const dim3 fold_grid(static_cast<uint32_t>(nfold));
-    auto stats = [&](const double *vec, int64_t k, double *res) {
-        const int64_t nch = (k + kStatChunk - 1) / kStatChunk;
-        hipLaunchKernelGGL(vec_stats_kernel, dim3(static_cast<uint32_t>(nch)), dim3(kT), 0, st,
-                           vec, k, spart);
-        hipLaunchKernelGGL(stats_fold_kernel, dim3(1), dim3(1), 0, st, spart, nch, res);
-    };
-
-    if (nc) {
-        // n <= 1024: iters + 2 passes over xi.  The first forms R = xi 1 and
-        // C = xi^T 1; the first power iteration (from v = C / |C|) also sums
-        // |xi|_F^2 and |xi - xi~|_F^2; the last pass forms |xi v| for the
-        // final unit vector v.
-        const dim3 grid(static_cast<uint32_t>(nblk));
-        launch_onepass<kPassSums>(nc, grid, st, xi, m, n, nullptr, nullptr, 0, nullptr, nullptr,
-                                  nullptr, 0.0, r, cpart, nullptr);
-        hipLaunchKernelGGL(col_fold_kernel, fold_grid, dim3(kT), 0, st, cpart, n, nblk, c, cfold);
-        stats(r, m, stats_r);
-        const double *vin = c, *vin_fold = cfold;
-        for (int it = 0; it < power_iters; ++it) {
-            if (it == 0) {
-                launch_onepass<kPassPowerErr>(nc, grid, st, xi, m, n, vin, vin_fold, nfold, r, c,
-                                              stats_r, eps_stab, nullptr, cpart, epart);
-                hipLaunchKernelGGL(err_fold_kernel, dim3(1), dim3(kT), 0, st, epart, nblk, err);
-            } else {
-                launch_onepass<kPassPower>(nc, grid, st, xi, m, n, vin, vin_fold, nfold, nullptr,
-                                           nullptr, nullptr, 0.0, nullptr, cpart, nullptr);
-            }
-            hipLaunchKernelGGL(col_fold_kernel, fold_grid, dim3(kT), 0, st, cpart, n, nblk, v,
-                               vfold);
-            vin = v;
-            vin_fold = vfold;
+    if (sh.nblk) {
+        // power_iters + 2 passes over xi.  The first forms C = xi^T 1; the
+        // first power iteration (from v = C) also sums |xi|_F^2 and
+        // |xi - xi~|_F^2; the last pass forms |xi v| for the final unit
+        // vector v.
+        double *c = buf, *v = c + sh.stride, *cpart = v + sh.stride;
+        double *cfold = cpart + sh.nblk * sh.stride, *vfold = cfold + 2 * sh.nfold;
+        double *epart = vfold + 2 * sh.nfold, *upart = epart + 2 * sh.nblk;
+        stats_r = upart + 2 * sh.nblk;
+        OnePass a{xi, m, n, sh.rows, nfold, nullptr, nullptr, eps_stab, cpart, epart, sh.stride};
+        auto fold = [&](double *out, double *parts) {
+            hipLaunchKernelGGL(col_fold_kernel, fold_grid, dim3(kT), 0, st, cpart, sh.stride, n,
+                               sh.nblk, out, parts);
+        };
+        launch_onepass<kPassSums>(a, sh.nblk, st);
+        fold(c, cfold);
+        a.v = c;
+        a.vparts = cfold;
+        launch_onepass<kPassPowerErr>(a, sh.nblk, st);
+        fold(v, vfold);
+        a.v = v;
+        a.vparts = vfold;
+        for (int it = 1; it < power_iters; ++it) {
+            launch_onepass<kPassPower>(a, sh.nblk, st);
+            fold(v, vfold);
         }
-        launch_onepass<kPassNorm>(nc, grid, st, xi, m, n, vin, vin_fold, nfold, nullptr, nullptr,
-                                  nullptr, 0.0, nullptr, cpart, epart);
-        hipLaunchKernelGGL(err_fold_kernel, dim3(1), dim3(kT), 0, st, epart, nblk, stats_u);
+        a.spart = upart;
+        launch_onepass<kPassNorm>(a, sh.nblk, st);
+        hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(kT), 0, st, cfold, nfold, upart, epart,
+                           sh.nblk, stats_r);
     } else {
+        const int64_t stripe = sh.stripe, nerr = sh.nerr;
+        const int nstripes = static_cast<int>(sh.nstripes);
+        double *r = buf, *c = r + m, *u = c + n, *v = u + m;
+        double *cpart = v + n, *epart = cpart + nstripes * n, *cfold = epart + 2 * nerr;
+        double *vfold = cfold + 2 * sh.nfold, *spart = vfold + 2 * sh.nfold;
+        stats_r = spart + 2 * sh.nstat;
+        double *stats_u = stats_r + 2, *err = stats_u + 2;
+        const dim3 rows_grid(static_cast<uint32_t>((m + kT / 64 - 1) / (kT / 64)));
+        const dim3 cols_grid(static_cast<uint32_t>(sh.ncb), static_cast<uint32_t>(nstripes));
+        auto stats = [&](const double *vec, int64_t k, double *res) {
+            const int64_t nch = (k + kStatChunk - 1) / kStatChunk;
+            hipLaunchKernelGGL(vec_stats_kernel, dim3(static_cast<uint32_t>(nch)), dim3(kT), 0, st,
+                               vec, k, spart);
+            hipLaunchKernelGGL(stats_fold_kernel, dim3(1), dim3(1), 0, st, spart, nch, res);
+        };
         // Shadow factors R = xi 1, C = xi^T 1 and the sum of R.
         hipLaunchKernelGGL(row_reduce_kernel, rows_grid, dim3(kT), 0, st, xi, m, n, nullptr,
-                           nullptr, int64_t(0), r);
+                           nullptr, 0, r);
         hipLaunchKernelGGL(col_partial_kernel, cols_grid, dim3(kT), 0, st, xi, m, n, stripe,
                            nullptr, cpart);
-        hipLaunchKernelGGL(col_fold_kernel, fold_grid, dim3(kT), 0, st, cpart, n, nstripes, c,
+        hipLaunchKernelGGL(col_fold_kernel, fold_grid, dim3(kT), 0, st, cpart, n, n, nstripes, c,
                            cfold);
         stats(r, m, stats_r);
         // |xi|_F^2 and |xi - xi~|_F^2
@@ -612,7 +831,7 @@ rikfad_status report_on(const float *xi, int64_t m, int64_t n, double eps_stab,
                                vin_fold, nfold, u);
             hipLaunchKernelGGL(col_partial_kernel, cols_grid, dim3(kT), 0, st, xi, m, n, stripe,
                                u, cpart);
-            hipLaunchKernelGGL(col_fold_kernel, fold_grid, dim3(kT), 0, st, cpart, n, nstripes,
+            hipLaunchKernelGGL(col_fold_kernel, fold_grid, dim3(kT), 0, st, cpart, n, n, nstripes,
                                v, vfold);
             vin = v;
             vin_fold = vfold;
@@ -622,8 +841,8 @@ rikfad_status report_on(const float *xi, int64_t m, int64_t n, double eps_stab,
                            vin_fold, nfold, u);
         stats(u, m, stats_u);
     }
-    // stats_r, stats_u and err are adjacent: one copy brings all three back
-    // (host[] keeps the order R, errors, u).
+    // The six results are adjacent: one copy brings them back (host[] keeps
+    // the order R, errors, u).
     hipError_t e = hipGetLastError();
     double res[6];
     if (e == hipSuccess) e = hipMemcpyAsync(res, stats_r, sizeof(res), hipMemcpyDeviceToHost, st);
@@ -654,7 +873,6 @@ rikfad_status report_on(const float *xi, int64_t m, int64_t n, double eps_stab,
 // obtain with hipGetSymbolAddress (the array's name in host code is only a
 // stand-in for the symbol, not a device address).  The address is looked up
 // once per device, with that device current, on the first call there.
-constexpr int64_t kScratchWords = int64_t(1) << 21;    // 16 MiB of doubles
 
 }  // namespace
 
