@@ -63,10 +63,11 @@ typedef enum { RIKFAD_FP32 = 0, RIKFAD_BF16 = 1 } rikfad_dtype;
  * create to destroy, zero-fills p, r and c before the first step (the paper
  * starts from R = C = 0) unless it resumes a saved state, and never lets two
  * tensors of one context share memory.  Every pointer must be aligned to its
- * element size.  A matrix with n a multiple of 4 and x, g, p 16-byte aligned
- * (fp32), or x, g 8-byte and p 16-byte aligned (bf16), takes the 4-wide
- * path (128-bit accesses, 64-bit for bf16 x and g); any other matrix a
- * one-column path in the same launch. */
+ * element size.  Matrices with n >= 4 take 4-wide accesses (128-bit, 64-bit
+ * for bf16 x and g), aligned to their size where n is a multiple of 4 and x,
+ * g, p are 16-byte aligned (fp32), or x, g 8-byte and p 16-byte aligned
+ * (bf16), and otherwise at element alignment; matrices of 2 or 3 columns take
+ * a one-column path in the same launch. */
 typedef struct {
     void *x;
     const void *g;
@@ -97,7 +98,7 @@ typedef struct rikfad_ctx rikfad_ctx;
  * step does nothing).  Validates every argument before any HIP call, builds
  * the device tile tables and allocates the partial-sum workspace on the
  * current HIP device: 4 (m B + S n + ceil(m / 256)) bytes per matrix for its
- * B column blocks (256 columns, or 64 on the one-column path) and S row
+ * B column blocks (at most 256 columns, 64 on the one-column path) and S row
  * stripes (32 rows; 16 in a set with fewer matrix tiles than the chip has
  * compute units; taller for narrow matrices) -- about 0.14 m n bytes
  * (rikfad_query reports the total).  The tensors and every stream passed to

@@ -48,12 +48,13 @@ static_assert(kReadBatch >= 1 && kReadBatch <= 32, "read batch");
 struct Lanes {
     int lane, llog, L, G, seg, nr, nld;
     bool colok;
-    int64_t col, lcol, r0;
+    int skip;          // ragged rows: the lane owns elements skip .. V - 1 of its access
+    int64_t lcol, r0;
     int64_t r_any;     // a row of the tile this wave may read: r0, or the tile's first row
 };
 
-template <int V>
-__device__ __forceinline__ Lanes lanes_of(const Tile &tile)
+template <int V, bool RAG>
+__device__ __forceinline__ Lanes lanes_of(const Tile &tile, int64_t n)
 {
     Lanes t;
     t.lane = threadIdx.x & (kWave - 1);
@@ -63,8 +64,13 @@ __device__ __forceinline__ Lanes lanes_of(const Tile &tile)
     t.seg = t.lane >> t.llog;
     const int ccol = (t.lane & (t.L - 1)) * V;
     t.colok = ccol < tile.ncols;
-    t.col = tile.col0 + ccol;
-    t.lcol = t.colok ? t.col : tile.col0;   // lanes past the block read its first column
+    t.lcol = t.colok ? tile.col0 + ccol : tile.col0;   // lanes past the block read its first
+    t.skip = 0;
+    if (RAG) {                              // see the R-iKFAD streaming pass
+        const int64_t c = t.lcol;
+        t.lcol = min(c, n - V);
+        t.skip = static_cast<int>(c - t.lcol);
+    }
     t.r0 = tile.start + static_cast<int64_t>(threadIdx.x >> 6) * tile.rpw;
     t.nr = max(0, min(tile.rpw, static_cast<int>(tile.start + tile.count - t.r0)));
     t.nld = (t.nr + t.G - 1) >> (6 - t.llog);
@@ -194,7 +200,7 @@ __device__ __forceinline__ float tile_factors(const TensorDesc &td, const Lanes 
                                               const float *__restrict__ ws, float (&fc)[V])
 {
 #pragma unroll
-    for (int i = 0; i < V; ++i) fc[i] = t.colok ? col_factor(gmem(td.c)[t.col + i]) : 0.f;
+    for (int i = 0; i < V; ++i) fc[i] = t.colok ? col_factor(gmem(td.c)[t.lcol + i]) : 0.f;
     const float s = sum_r(ws + td.chunk, td.nchunk);
     const float inv_s = s > 0.f ? 1.f / s : 0.f;
     return t.lane < t.nr ? row_factor(gmem(td.r)[t.r0 + t.lane], inv_s) : 0.f;
@@ -259,7 +265,7 @@ __device__ __forceinline__ void flat_tile(const Tile &tile, Op &op)
 
 // ---------------------------------------------------------------- pass 1
 
-template <typename XT, int V, bool X2>
+template <typename XT, int V, bool X2, bool RAG>
 __device__ void stats_matrix(const TensorDesc &td, const XT *__restrict__ g, const Tile &tile,
                              float *__restrict__ ws, const AdaCoeffs &k, float *lds, float &x2)
 {
@@ -270,7 +276,7 @@ __device__ void stats_matrix(const TensorDesc &td, const XT *__restrict__ g, con
     // after its last batch.
     constexpr int B = X2 ? (kReadBatch + 1) / 2 : kReadBatch;
     static_assert(kRowChunk % B == 0, "whole batches per row chunk");
-    const Lanes t = lanes_of<V>(tile);
+    const Lanes t = lanes_of<V, RAG>(tile, td.n);
     const XT *__restrict__ x = static_cast<const XT *>(td.x);
     const int64_t n = td.n;
     float acc[V];
@@ -299,7 +305,8 @@ __device__ void stats_matrix(const TensorDesc &td, const XT *__restrict__ g, con
                     float rs = 0.f;
 #pragma unroll
                     for (int i = 0; i < V; ++i) {
-                        const float q = ok ? gv[i] * gv[i] + k.eps1 : 0.f;
+                        const bool own = ok && (!RAG || i >= t.skip);
+                        const float q = own ? gv[i] * gv[i] + k.eps1 : 0.f;
                         acc[i] += q;
                         rs += q;
                     }
@@ -308,14 +315,15 @@ __device__ void stats_matrix(const TensorDesc &td, const XT *__restrict__ g, con
                         float xv[V];
                         Raw<XT, V>::unpack(xr[u], xv);
 #pragma unroll
-                        for (int i = 0; i < V; ++i) x2 += ok ? xv[i] * xv[i] : 0.f;
+                        for (int i = 0; i < V; ++i)
+                            x2 += ok && (!RAG || i >= t.skip) ? xv[i] * xv[i] : 0.f;
                     }
                 }
             }
         }
         park_rows(a, c0, t, myrow);
     }
-    store_partials<V>(td, tile, ws, acc, myrow, t.nr, t.r0, lds);
+    store_partials<V>(td, tile, ws, acc, myrow, t.nr, t.r0, lds, t.skip);
 }
 
 // Unfactored second moment: v <- b v + (1-b)(G^2 + eps1); sums of U^2 with
@@ -350,7 +358,7 @@ struct StatsVec {
     }
 };
 
-template <typename XT, int V, bool X2>
+template <typename XT, int V, bool RAG, bool X2>
 __global__ __launch_bounds__(kStreamThreads) void adafm_stats_kernel(
     const TensorDesc *__restrict__ tensors, const void *const *__restrict__ grads,
     const Tile *__restrict__ tiles, int64_t tile0, float *__restrict__ ws,
@@ -369,9 +377,11 @@ __global__ __launch_bounds__(kStreamThreads) void adafm_stats_kernel(
         u2 = op.u2;
         x2 = op.x2;
     } else if (V > 1 && tile.vec == 1) {
-        stats_matrix<XT, 1, X2>(td, g, tile, ws, k, lds, x2);
+        stats_matrix<XT, 1, X2, false>(td, g, tile, ws, k, lds, x2);
+    } else if (RAG && tile.ragged) {
+        stats_matrix<XT, V, X2, RAG>(td, g, tile, ws, k, lds, x2);
     } else {
-        stats_matrix<XT, V, X2>(td, g, tile, ws, k, lds, x2);
+        stats_matrix<XT, V, X2, false>(td, g, tile, ws, k, lds, x2);
     }
     block_sum2<kStreamWaves>(u2, x2, red);
     if (threadIdx.x == 0) {
@@ -385,12 +395,12 @@ __global__ __launch_bounds__(kStreamThreads) void adafm_stats_kernel(
 // Sum of U^2 over one matrix tile (this lane's share), in batches of row
 // loads as in the statistics pass.  The first batch goes out before the
 // factor loads, so their round trips overlap.
-template <typename XT, int V>
+template <typename XT, int V, bool RAG>
 __device__ float rms_matrix(const TensorDesc &td, const XT *__restrict__ g, const Tile &tile,
                             const float *__restrict__ ws)
 {
     constexpr int B = kReadBatch;
-    const Lanes t = lanes_of<V>(tile);
+    const Lanes t = lanes_of<V, RAG>(tile, td.n);
     typename Raw<XT, V>::type gr[B];
     float u2 = 0.f;
     auto issue = [&](int ld0) {
@@ -415,7 +425,7 @@ __device__ float rms_matrix(const TensorDesc &td, const XT *__restrict__ g, cons
 #pragma unroll
             for (int i = 0; i < V; ++i) {
                 const float uu = (gv[i] * fr) * fc[i];
-                u2 += ok ? uu * uu : 0.f;
+                u2 += ok && (!RAG || i >= t.skip) ? uu * uu : 0.f;
             }
         }
     };
@@ -427,7 +437,7 @@ __device__ float rms_matrix(const TensorDesc &td, const XT *__restrict__ g, cons
     return u2;
 }
 
-template <typename XT, int V>
+template <typename XT, int V, bool RAG>
 __global__ __launch_bounds__(kStreamThreads) void adafm_rms_kernel(
     const TensorDesc *__restrict__ tensors, const void *const *__restrict__ grads,
     const Tile *__restrict__ tiles, int64_t tile0, const float *__restrict__ ws,
@@ -439,8 +449,9 @@ __global__ __launch_bounds__(kStreamThreads) void adafm_rms_kernel(
     if (tile.kind == KIND_VECTOR) return;   // vector sums are complete after pass 1
     const TensorDesc td = tensors[tile.tensor];
     const XT *__restrict__ g = static_cast<const XT *>(grads[tile.tensor]);
-    float u2 = V > 1 && tile.vec == 1 ? rms_matrix<XT, 1>(td, g, tile, ws)
-                                      : rms_matrix<XT, V>(td, g, tile, ws);
+    float u2 = V > 1 && tile.vec == 1 ? rms_matrix<XT, 1, false>(td, g, tile, ws)
+               : RAG && tile.ragged   ? rms_matrix<XT, V, RAG>(td, g, tile, ws)
+                                      : rms_matrix<XT, V, false>(td, g, tile, ws);
     float zero = 0.f;
     block_sum2<kStreamWaves>(u2, zero, red);
     if (threadIdx.x == 0) gmem(tilepart)[2 * ti] = u2;
@@ -479,12 +490,12 @@ __global__ __launch_bounds__(kThreads) void adafm_scale_kernel(
 template <typename XT> struct UpdateRing { static constexpr int value = kRingF32; };
 template <> struct UpdateRing<uint16_t> { static constexpr int value = kRingBF16; };
 
-template <typename XT, int V>
+template <typename XT, int V, bool RAG>
 __device__ void update_matrix(const TensorDesc &td, const XT *__restrict__ g, const Tile &tile,
                               const float *__restrict__ ws, float s, const AdaCoeffs &k)
 {
     constexpr int B = UpdateRing<XT>::value;
-    const Lanes t = lanes_of<V>(tile);
+    const Lanes t = lanes_of<V, RAG>(tile, td.n);
     XT *__restrict__ x = static_cast<XT *>(td.x);
     float *__restrict__ mom = td.p;
     const int64_t n = td.n;
@@ -517,9 +528,14 @@ __device__ void update_matrix(const TensorDesc &td, const XT *__restrict__ g, co
                 xv[i] = xv[i] - mv[u][i];
             }
             if (t.colok && rl < t.nr) {
-                const int64_t off = (t.r0 + rl) * n + t.col;
-                Io<XT, V>::store(x + off, xv);
-                Io<float, V>::store(mom + off, mv[u]);
+                const int64_t off = (t.r0 + rl) * n + t.lcol;
+                if constexpr (RAG) {
+                    store_owned<XT>(x + off, xv, t.skip);
+                    store_owned<float>(mom + off, mv[u], t.skip);
+                } else {
+                    Io<XT, V>::store(x + off, xv);
+                    Io<float, V>::store(mom + off, mv[u]);
+                }
             }
             if (ld + B < t.nld) {
                 const int64_t off = row_off(t, (ld + B) * t.G + t.seg, n);
@@ -559,7 +575,7 @@ struct UpdateVec {
     }
 };
 
-template <typename XT, int V>
+template <typename XT, int V, bool RAG>
 __global__ __launch_bounds__(kStreamThreads) void adafm_update_kernel(
     const TensorDesc *__restrict__ tensors, const void *const *__restrict__ grads,
     const Tile *__restrict__ tiles, int64_t tile0, const float *__restrict__ ws,
@@ -574,20 +590,25 @@ __global__ __launch_bounds__(kStreamThreads) void adafm_update_kernel(
         flat_tile(tile, op);
         return;
     }
-    if (V > 1 && tile.vec == 1) update_matrix<XT, 1>(td, g, tile, ws, s, k);
-    else update_matrix<XT, V>(td, g, tile, ws, s, k);
+    if (V > 1 && tile.vec == 1) update_matrix<XT, 1, false>(td, g, tile, ws, s, k);
+    else if (RAG && tile.ragged) update_matrix<XT, V, RAG>(td, g, tile, ws, s, k);
+    else update_matrix<XT, V, false>(td, g, tile, ws, s, k);
 }
 
-// Kernel instantiation for a tile group's (storage type, width); a wide
-// one also serves the group's one-column tiles.  nullptr for a combination
-// the planner does not produce.
+// Kernel instantiation for a tile group's (storage type, width, ragged
+// tiles or none); a wide one also serves the group's one-column tiles.
+template <typename F, typename XT, typename Pick>
+F pick_width(const TileGroup &gr, Pick p)
+{
+    return gr.ragged     ? p.template get<XT, 4, true>()
+           : gr.vec == 4 ? p.template get<XT, 4, false>()
+                         : p.template get<XT, 1, false>();
+}
+
 template <typename F, typename Pick>
 F pick(const TileGroup &gr, Pick p)
 {
-    if (gr.dtype == DT_F32) return gr.vec == 4 ? p.template get<float, 4>()
-                                : gr.vec == 1 ? p.template get<float, 1>() : nullptr;
-    return gr.vec == 4 ? p.template get<uint16_t, 4>()
-         : gr.vec == 1 ? p.template get<uint16_t, 1>() : nullptr;
+    return gr.dtype == DT_F32 ? pick_width<F, float>(gr, p) : pick_width<F, uint16_t>(gr, p);
 }
 
 typedef void (*StatsFn)(const TensorDesc *, const void *const *, const Tile *, int64_t, float *,
@@ -598,13 +619,19 @@ typedef void (*UpdateFn)(const TensorDesc *, const void *const *, const Tile *, 
                          const float *, const float *, AdaCoeffs);
 
 template <bool X2> struct PickStats {
-    template <typename XT, int V> StatsFn get() const { return adafm_stats_kernel<XT, V, X2>; }
+    template <typename XT, int V, bool RAG> StatsFn get() const
+    {
+        return adafm_stats_kernel<XT, V, RAG, X2>;
+    }
 };
 struct PickRms {
-    template <typename XT, int V> RmsFn get() const { return adafm_rms_kernel<XT, V>; }
+    template <typename XT, int V, bool RAG> RmsFn get() const { return adafm_rms_kernel<XT, V, RAG>; }
 };
 struct PickUpdate {
-    template <typename XT, int V> UpdateFn get() const { return adafm_update_kernel<XT, V>; }
+    template <typename XT, int V, bool RAG> UpdateFn get() const
+    {
+        return adafm_update_kernel<XT, V, RAG>;
+    }
 };
 
 }  // namespace
@@ -620,7 +647,6 @@ hipError_t launch_adafm_stats(const TensorDesc *tensors, const void *const *grad
         if (gr.count <= 0) continue;
         const StatsFn fn = x2 ? pick<StatsFn>(gr, PickStats<true>())
                               : pick<StatsFn>(gr, PickStats<false>());
-        if (!fn) return hipErrorInvalidValue;
         hipEvent_t a = start, b = q == last ? stop : nullptr;
         start = nullptr;
         const hipError_t e = launch(fn, dim3(static_cast<uint32_t>(gr.count)),
@@ -641,7 +667,6 @@ hipError_t launch_adafm_rms(const TensorDesc *tensors, const void *const *grads,
         const TileGroup &gr = groups[q];
         if (gr.count <= 0) continue;
         const RmsFn fn = pick<RmsFn>(gr, PickRms());
-        if (!fn) return hipErrorInvalidValue;
         hipEvent_t a = start, b = q == last ? stop : nullptr;
         start = nullptr;
         const hipError_t e = launch(fn, dim3(static_cast<uint32_t>(gr.count)),
@@ -671,7 +696,6 @@ hipError_t launch_adafm_update(const TensorDesc *tensors, const void *const *gra
         const TileGroup &gr = groups[q];
         if (gr.count <= 0) continue;
         const UpdateFn fn = pick<UpdateFn>(gr, PickUpdate());
-        if (!fn) return hipErrorInvalidValue;
         hipEvent_t a = start, b = q == last ? stop : nullptr;
         start = nullptr;
         const hipError_t e = launch(fn, dim3(static_cast<uint32_t>(gr.count)),

@@ -47,6 +47,29 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+// The same, at element alignment: rows of any length start at any element.
+// gfx950 takes them as the same single 16-byte (8-byte) accesses, so the
+// 4-wide accesses below use them throughout.
+typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2e __attribute__((ext_vector_type(2), aligned(2)));
+
+__device__ __forceinline__ f32x4 ldg4(const float *q)
+{
+    return __builtin_nontemporal_load((const RK_GLOBAL f32x4e *)q);
+}
+__device__ __forceinline__ void stg4(float *q, f32x4 v)
+{
+    __builtin_nontemporal_store(v, (RK_GLOBAL f32x4e *)q);
+}
+__device__ __forceinline__ u32x2 ldg4(const uint16_t *q)
+{
+    return __builtin_nontemporal_load((const RK_GLOBAL u32x2e *)q);
+}
+__device__ __forceinline__ void stg4(uint16_t *q, u32x2 v)
+{
+    __builtin_nontemporal_store(v, (RK_GLOBAL u32x2e *)q);
+}
+
 // ------------------------------------------------------------------ bf16
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b)
@@ -71,12 +94,12 @@ template <typename T, int V> struct Io;
 template <> struct Io<float, 4> {
     static __device__ __forceinline__ void load(const float *q, float (&o)[4])
     {
-        const f32x4 v = ldg(reinterpret_cast<const f32x4 *>(q));
+        const f32x4 v = ldg4(q);
         o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
     }
     static __device__ __forceinline__ void store(float *q, const float (&o)[4])
     {
-        stg(reinterpret_cast<f32x4 *>(q), f32x4{o[0], o[1], o[2], o[3]});
+        stg4(q, f32x4{o[0], o[1], o[2], o[3]});
     }
 };
 
@@ -125,7 +148,7 @@ template <> struct Io<uint16_t, 8> {
 template <> struct Io<uint16_t, 4> {
     static __device__ __forceinline__ void load(const uint16_t *q, float (&o)[4])
     {
-        const u32x2 v = ldg(reinterpret_cast<const u32x2 *>(q));
+        const u32x2 v = ldg4(q);
         o[0] = __uint_as_float(v.x << 16); o[1] = __uint_as_float(v.x & 0xffff0000u);
         o[2] = __uint_as_float(v.y << 16); o[3] = __uint_as_float(v.y & 0xffff0000u);
     }
@@ -135,7 +158,7 @@ template <> struct Io<uint16_t, 4> {
                            (static_cast<uint32_t>(f32_to_bf16(o[1])) << 16);
         const uint32_t b = static_cast<uint32_t>(f32_to_bf16(o[2])) |
                            (static_cast<uint32_t>(f32_to_bf16(o[3])) << 16);
-        stg(reinterpret_cast<u32x2 *>(q), u32x2{a, b});
+        stg4(q, u32x2{a, b});
     }
 };
 
@@ -152,7 +175,7 @@ template <> struct Raw<float, 4> {
     typedef f32x4 type;
     static __device__ __forceinline__ type load(const float *q)
     {
-        return ldg(reinterpret_cast<const f32x4 *>(q));
+        return ldg4(q);
     }
     static __device__ __forceinline__ void unpack(const type &v, float (&o)[4])
     {
@@ -170,7 +193,7 @@ template <> struct Raw<uint16_t, 4> {
     typedef u32x2 type;
     static __device__ __forceinline__ type load(const uint16_t *q)
     {
-        return ldg(reinterpret_cast<const u32x2 *>(q));
+        return ldg4(q);
     }
     static __device__ __forceinline__ void unpack(const type &v, float (&o)[4])
     {
@@ -215,17 +238,33 @@ __device__ __forceinline__ float damp(float v, const Coeffs &k)
     return __builtin_fmaf(v, k.dm1, v);
 }
 
+// Stores the elements a lane of a ragged row owns, skip .. 3 of its four.
+template <typename T>
+__device__ __forceinline__ void store_owned(T *q, const float (&o)[4], int skip)
+{
+    if (skip == 0) {
+        Io<T, 4>::store(q, o);
+        return;
+    }
+#pragma unroll
+    for (int i = 1; i < 4; ++i)
+        if (i >= skip) Io<T, 1>::store(q + i, {o[i]});
+}
+
 // Stage 1 of the row and column sums of a matrix tile, after each wave has
 // walked its rows.  acc[V]: this lane's column sums; myrow: in lane t, the
 // sum of the wave's row r0 + t (t < nr).  Lanes l and l ^ o (o >= L) own the
 // same columns and are folded first, then the waves through LDS in wave
 // order; the tile writes its column partials (stripe `stripe` of colpart) and
-// each wave its row partials (row `cb` of rowpart).  Every thread of the
-// workgroup must call this (it synchronises the workgroup).
+// each wave its row partials (row `cb` of rowpart).  A lane of a ragged row
+// owns the elements skip .. V - 1 of its acc, which end with its columns.
+// Every thread of the workgroup must call this (it synchronises the
+// workgroup).
 template <int V>
 __device__ __forceinline__ void store_partials(const TensorDesc &td, const Tile &tile,
                                                float *__restrict__ ws, float (&acc)[V],
-                                               float myrow, int nr, int64_t r0, float *lds)
+                                               float myrow, int nr, int64_t r0, float *lds,
+                                               int skip = 0)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
@@ -237,7 +276,8 @@ __device__ __forceinline__ void store_partials(const TensorDesc &td, const Tile 
     }
     if (lane < L && ccol < tile.ncols) {
 #pragma unroll
-        for (int i = 0; i < V; ++i) lds[wave * kWave * V + ccol + i] = acc[i];
+        for (int i = 0; i < V; ++i)
+            if (i >= skip) lds[wave * kWave * V + ccol - skip + i] = acc[i];
     }
     __syncthreads();
     float *colpart = ws + td.colpart;

@@ -64,7 +64,19 @@ __device__ __forceinline__ void load_row(const XT *x, const XT *g, const float *
 template <typename XT> struct RingDepth { static constexpr int value = kRingF32; };
 template <> struct RingDepth<uint16_t> { static constexpr int value = kRingBF16; };
 
-template <typename XT, int V>
+//
+// RAG: a ragged row's last lane can hold fewer than V columns.  It then reads
+// the row's last V elements and owns the last V - skip of them; the others
+// are another lane's (or another workgroup's, which may be rewriting them):
+// they are masked out of the sums and not stored.  Against the one-column
+// path that such rows took before (4-byte, bf16 2-byte loads, 64-column
+// blocks): 768 x 50257 and 8 matrices of 769 columns 258 -> 159 us in bf16
+// (finalisation 81 -> 6.4 us, a quarter of the blocks), with the same fp32 set
+// 336 -> 223 us per step.  What is left against rows of whole lines (5.6
+// TB/s; 4.2-5.0 here) is the 128-byte lines that two blocks share: both
+// fetch them and write them in part.  Plain instead of non-temporal accesses,
+// which could merge in L2, are 2-6% slower in fp32.
+template <typename XT, int V, bool RAG>
 __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
                               const Tile &tile, float *__restrict__ ws,
                               const Coeffs &k, int pending, float *lds)
@@ -80,7 +92,13 @@ __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
     const int64_t n = td.n;
     const int ccol = sl * V;
     const bool colok = ccol < tile.ncols;
-    const int64_t col = tile.col0 + ccol;
+    int64_t col = tile.col0 + ccol;
+    int skip = 0;
+    if (RAG) {
+        const int64_t c = col;
+        col = min(c, n - V);
+        skip = colok ? static_cast<int>(c - col) : 0;
+    }
     const int64_t r0 = tile.start + static_cast<int64_t>(wave) * tile.rpw;
     const int nr = max(0, min(tile.rpw, static_cast<int>(tile.start + tile.count - r0)));
     const int nld = (nr + G - 1) >> (6 - llog);   // row loads of this wave
@@ -106,8 +124,8 @@ __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
     // requests per stream in flight.
     typename Raw<XT, V>::type xr[B], gr[B];
     float qv[B][V];
-    // A lane outside the block's columns reads the block's first column.
-    const int64_t lcol = colok ? col : tile.col0;
+    // A lane outside the block's columns reads the block's first ones.
+    const int64_t lcol = colok ? col : RAG ? min<int64_t>(tile.col0, n - V) : tile.col0;
 #pragma unroll
     for (int u = 0; u < B; ++u)
         if (nr > 0)
@@ -132,22 +150,28 @@ __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
             float rs = 0.f;
 #pragma unroll
             for (int i = 0; i < V; ++i) {
-                const float q = ok ? qv[u][i] : 0.f;
-                const float gg = ok ? gv[i] : 0.f;
+                const bool own = ok && (!RAG || i >= skip);
+                const float q = own ? qv[u][i] : 0.f;
+                const float gg = own ? gv[i] : 0.f;
                 const float e = exp2f(rate * cv[i]);
                 const float pn = pending ? damp(q * e, k) : q;
                 const float pb = kick(pn, gg, k);
                 xv[i] = xv[i] + k.h * pb;
                 const float p1 = pb * e;
                 qv[u][i] = p1;
-                const float sq = ok ? p1 * p1 : 0.f;
+                const float sq = own ? p1 * p1 : 0.f;
                 acc[i] += sq;
                 rs += sq;
             }
             if (ok) {
                 const int64_t off = (r0 + rl) * n + col;
-                Io<XT, V>::store(x + off, xv);
-                Io<float, V>::store(p + off, qv[u]);
+                if constexpr (RAG) {
+                    store_owned<XT>(x + off, xv, skip);
+                    store_owned<float>(p + off, qv[u], skip);
+                } else {
+                    Io<XT, V>::store(x + off, xv);
+                    Io<float, V>::store(p + off, qv[u]);
+                }
             }
             const int rn = (ld + B) * G + seg;
             if (ld + B < nld)
@@ -159,7 +183,7 @@ __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
         }
     }
 
-    store_partials<V>(td, tile, ws, acc, myrow, nr, r0, lds);
+    store_partials<V>(td, tile, ws, acc, myrow, nr, r0, lds, skip);
 }
 
 // ------------------------------------------- element-wise iKFAD (vectors)
@@ -263,8 +287,9 @@ __device__ void elementwise_tile(const TensorDesc &td, const void *g, const Tile
 
 // One instantiation per (storage type, access width) of the matrix tiles it
 // serves, so each carries only the registers its own path needs; vector
-// tiles of the same storage type ride along (element-wise iKFAD).
-template <typename XT, int V>
+// tiles of the same storage type ride along (element-wise iKFAD).  RAG: the
+// launch has ragged tiles (more registers than the whole-access path).
+template <typename XT, int V, bool RAG>
 __global__ __launch_bounds__(kStreamThreads) void rikfad_stream_kernel(
     const TensorDesc *__restrict__ tensors, const void *const *__restrict__ grads,
     const Tile *__restrict__ tiles, int64_t tile0, int64_t ntile, float *__restrict__ ws,
@@ -279,11 +304,13 @@ __global__ __launch_bounds__(kStreamThreads) void rikfad_stream_kernel(
         return;
     }
     // Tensors whose rows break 16-byte alignment ride along in the same
-    // launch on the one-column path (fewer registers than the wide path).
+    // launch: ragged tiles, or the one-column path for rows of 2 or 3.
     if (V > 1 && tile.vec == 1)
-        stream_matrix<XT, 1>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
+        stream_matrix<XT, 1, false>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
+    else if (RAG && tile.ragged)
+        stream_matrix<XT, V, RAG>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
     else
-        stream_matrix<XT, V>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
+        stream_matrix<XT, V, false>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
 }
 
 // Finalisation (C.2 / C.3 stage 2), one launch of T-thread workgroups.
@@ -306,7 +333,7 @@ __global__ __launch_bounds__(1 << LOG2T) void rikfad_finalize_kernel(
 {
     constexpr int T = 1 << LOG2T;
     static_assert(kChunkRows == 4 * kWave, "a wave of row items covers one 256-row chunk");
-    __shared__ f32x4 lds[T / kWave * 4];
+    __shared__ f32x4 lds[T];
     const FinItem it = items[blockIdx.x];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
@@ -357,6 +384,53 @@ __global__ __launch_bounds__(1 << LOG2T) void rikfad_finalize_kernel(
         if (lane == 0 && wave * kChunkRows < it.count) {
             gmem(ws)[it.chunk + wave] = v;
             bad = bad || !isfinite(v);
+        }
+    } else if (it.kind == FIN_ROWS_WIDE) {
+        // Rows start + 4 lane .. + 3 in every wave; the waves sum consecutive
+        // ranges of the blocks in order, then wave 0 adds the waves in order.
+        constexpr int W = T / kWave, NL = kFinWideLoads(T);
+        const int t0 = 4 * lane;
+        const int64_t i0 = static_cast<int64_t>(it.start) + t0;
+        const int per = (it.nparts + W - 1) / W;
+        const int b0 = min(wave * per, it.nparts), b1 = min(b0 + per, it.nparts);
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+        if (!init_only && t0 < it.count) {
+            const int64_t stride = pad4(it.len) >> 2;
+            const RK_GLOBAL f32x4 *rp =
+                reinterpret_cast<const RK_GLOBAL f32x4 *>(gmem(ws) + it.part + i0);
+            for (int cb = b0; cb < b1; cb += NL) {
+                f32x4 v[NL];
+#pragma unroll
+                for (int u = 0; u < NL; ++u) {
+                    const f32x4 w = rp[static_cast<int64_t>(min(cb + u, b1 - 1)) * stride];
+                    v[u] = cb + u < b1 ? w : f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+#pragma unroll
+                for (int u = 0; u < NL; ++u) s += v[u];
+            }
+        }
+        lds[threadIdx.x] = s;
+        __syncthreads();
+        if (wave == 0) {
+            for (int w = 1; w < W; ++w) s += lds[w * kWave + lane];
+            const float sv[4] = {s.x, s.y, s.z, s.w};
+            float rv[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (t0 + j < it.count) {
+                    const float r = gmem(it.f)[i0 + j];
+                    rv[j] = init_only ? r : k.a * r + k.kappa * sv[j];
+                    if (!init_only) gmem(it.f)[i0 + j] = rv[j];
+                    bad = bad || !isfinite(rv[j]);
+                }
+            }
+            float v = ((rv[0] + rv[1]) + rv[2]) + rv[3];
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) v += __shfl_xor(v, o);
+            if (lane == 0) {
+                gmem(ws)[it.chunk] = v;
+                bad = bad || !isfinite(v);
+            }
         }
     } else {
         const int slog = it.lanes_log2;
@@ -423,7 +497,7 @@ __global__ __launch_bounds__(1 << LOG2T) void rikfad_finalize_kernel(
 
 // Second half-kick + D on stored P^(1): p <- d (p .* exp(-(h/2) xi~)) with
 // the current factors (App. A Table rows C.4 and D).
-template <int V>
+template <int V, bool RAG>
 __device__ void apply_matrix(const TensorDesc &td, const Tile &tile, const float *__restrict__ ws,
                              const Coeffs &k)
 {
@@ -437,7 +511,13 @@ __device__ void apply_matrix(const TensorDesc &td, const Tile &tile, const float
     const int64_t n = td.n;
     const int ccol = sl * V;
     const bool colok = ccol < tile.ncols;
-    const int64_t col = tile.col0 + ccol;
+    int64_t col = tile.col0 + ccol;
+    int skip = 0;
+    if (RAG) {                          // as in stream_matrix
+        const int64_t c = col;
+        col = min(c, n - V);
+        skip = static_cast<int>(c - col);
+    }
     float cv[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) cv[i] = colok ? gmem(td.c)[col + i] : 0.f;
@@ -456,12 +536,13 @@ __device__ void apply_matrix(const TensorDesc &td, const Tile &tile, const float
             Io<float, V>::load(p + off, qv);
 #pragma unroll
             for (int i = 0; i < V; ++i) qv[i] = damp(qv[i] * exp2f(rate * cv[i]), k);
-            Io<float, V>::store(p + off, qv);
+            if constexpr (RAG) store_owned<float>(p + off, qv, skip);
+            else Io<float, V>::store(p + off, qv);
         }
     }
 }
 
-template <int V>
+template <int V, bool RAG>
 __global__ __launch_bounds__(kStreamThreads) void rikfad_apply_kernel(
     const TensorDesc *__restrict__ tensors, const Tile *__restrict__ tiles, int64_t tile0,
     const float *__restrict__ ws, Coeffs k)
@@ -469,8 +550,9 @@ __global__ __launch_bounds__(kStreamThreads) void rikfad_apply_kernel(
     const Tile tile = tiles[tile0 + blockIdx.x];
     const TensorDesc td = tensors[tile.tensor];
     if (tile.kind != KIND_MATRIX) return;
-    if (V > 1 && tile.vec == 1) apply_matrix<1>(td, tile, ws, k);
-    else apply_matrix<V>(td, tile, ws, k);
+    if (V > 1 && tile.vec == 1) apply_matrix<1, false>(td, tile, ws, k);
+    else if (RAG && tile.ragged) apply_matrix<V, RAG>(td, tile, ws, k);
+    else apply_matrix<V, false>(td, tile, ws, k);
 }
 
 // Full-tensor iKFAD: every tile is an element range with its own friction.
@@ -697,17 +779,19 @@ hipError_t launch_stream(const TensorDesc *tensors, const void *const *grads, co
         const dim3 grid(static_cast<uint32_t>(gr.count)), block(kStreamThreads);
         hipEvent_t a = start, b = q == last ? stop : nullptr;
         start = nullptr;
+        auto go = [&](auto kernel) {
+            return launch(kernel, grid, block, stream, a, b, tensors, grads, tiles, gr.begin,
+                          gr.count, ws, k, pending, flag);
+        };
         hipError_t e;
         if (gr.dtype == DT_F32)
-            e = gr.vec == 4 ? launch(rikfad_stream_kernel<float, 4>, grid, block, stream, a, b,
-                                     tensors, grads, tiles, gr.begin, gr.count, ws, k, pending, flag)
-                            : launch(rikfad_stream_kernel<float, 1>, grid, block, stream, a, b,
-                                     tensors, grads, tiles, gr.begin, gr.count, ws, k, pending, flag);
+            e = gr.ragged     ? go(rikfad_stream_kernel<float, 4, true>)
+                : gr.vec == 4 ? go(rikfad_stream_kernel<float, 4, false>)
+                              : go(rikfad_stream_kernel<float, 1, false>);
         else
-            e = gr.vec == 4 ? launch(rikfad_stream_kernel<uint16_t, 4>, grid, block, stream, a,
-                                     b, tensors, grads, tiles, gr.begin, gr.count, ws, k, pending, flag)
-                            : launch(rikfad_stream_kernel<uint16_t, 1>, grid, block, stream, a,
-                                     b, tensors, grads, tiles, gr.begin, gr.count, ws, k, pending, flag);
+            e = gr.ragged     ? go(rikfad_stream_kernel<uint16_t, 4, true>)
+                : gr.vec == 4 ? go(rikfad_stream_kernel<uint16_t, 4, false>)
+                              : go(rikfad_stream_kernel<uint16_t, 1, false>);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -737,11 +821,12 @@ hipError_t launch_apply(const TensorDesc *tensors, const Tile *tiles, const Tile
         const dim3 grid(static_cast<uint32_t>(gr.count)), block(kStreamThreads);
         hipEvent_t a = start, b = q == last ? stop : nullptr;
         start = nullptr;
-        const hipError_t e =
-            gr.vec == 4 ? launch(rikfad_apply_kernel<4>, grid, block, stream, a, b, tensors,
-                                 tiles, gr.begin, ws, k)
-                        : launch(rikfad_apply_kernel<1>, grid, block, stream, a, b, tensors,
-                                 tiles, gr.begin, ws, k);
+        auto go = [&](auto kernel) {
+            return launch(kernel, grid, block, stream, a, b, tensors, tiles, gr.begin, ws, k);
+        };
+        const hipError_t e = gr.ragged     ? go(rikfad_apply_kernel<4, true>)
+                             : gr.vec == 4 ? go(rikfad_apply_kernel<4, false>)
+                                           : go(rikfad_apply_kernel<1, false>);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -38,6 +38,7 @@ constexpr int kBlockLanes = RK_BLOCK_LANES;     // lanes per row of a full colum
 constexpr int kRowsPerWave = RK_ROWS_PER_WAVE;  // rows per wave of a matrix tile
 constexpr int kChunkRows = kThreads;            // rows per partial sum of R
 constexpr int kSmallSetTiles = 256;             // compute units of the chip
+constexpr int kRaggedVec = 4;                   // elements per lane access of ragged rows
 constexpr int kVecIters = 4;                    // vector tile = kThreads*vec*kVecIters
 static_assert(kStreamWaves >= 1 && kStreamWaves <= 16, "a workgroup holds at most 16 waves");
 static_assert(kRingF32 >= 1 && kRingBF16 >= 1, "a ring holds at least one row load");
@@ -47,7 +48,7 @@ static_assert(kBlockLanes >= 1 && kBlockLanes <= kWave && (kBlockLanes & (kBlock
 
 enum : int32_t { DT_F32 = 0, DT_BF16 = 1 };
 enum : int32_t { KIND_MATRIX = 0, KIND_VECTOR = 1 };
-enum : int32_t { FIN_ROWS = 0, FIN_COLS = 1 };
+enum : int32_t { FIN_ROWS = 0, FIN_COLS = 1, FIN_ROWS_WIDE = 2 };
 
 // Finalisation workgroups: 256 threads, or 1024 for sets with a matrix of
 // more than 512 row stripes (about 16K rows), whose column items need more
@@ -67,6 +68,14 @@ constexpr int kFinLargeLog2 = RK_FIN_LARGE_LOG2;
 #endif
 constexpr int kFinLoads = RK_FIN_LOADS;         // 16-byte column partial loads in flight per thread
 constexpr int kFinRowLoads = RK_FIN_ROW_LOADS;  // the same for row partials (row items)
+// Row items are split over more workgroups above this many column blocks.
+#ifndef RK_FIN_WIDE_BLOCKS
+#define RK_FIN_WIDE_BLOCKS 16
+#endif
+constexpr int kFinWideBlocks = RK_FIN_WIDE_BLOCKS;
+// 16-byte loads in flight per thread of such items: few where 16 waves share
+// the blocks, so that two 1024-thread workgroups still fit a compute unit.
+constexpr int kFinWideLoads(int threads) { return threads > 256 ? 4 : 16; }
 static_assert(kFinLargeLog2 >= kFinSmallLog2 && kFinLargeLog2 <= 10, "finalisation workgroup");
 
 // Row partials are [ncb][pad4(m)]: each block's row sums padded to a
@@ -104,7 +113,7 @@ struct Tile {
     int32_t tensor;
     int32_t count;     // matrix: rows (<= kStreamWaves * rpw); vector: elements
     int32_t col0;      // matrix: first column of the block
-    int32_t ncols;     // matrix: columns of the block (multiple of vec)
+    int32_t ncols;     // matrix: columns of the block (multiple of vec, unless ragged)
     int32_t stripe;    // matrix: row-stripe index (row of the column partials)
     int32_t cb;        // matrix: column-block index (row of the row partials)
     int32_t lanes_log2;// matrix: log2 of lanes per row (rows per load = 64 >> it)
@@ -112,19 +121,21 @@ struct Tile {
     int32_t vec;       // elements per lane access: 1, 4 or 8
     int32_t dtype;
     int32_t rpw;       // matrix: rows per wave (<= kMaxRowsPerWave)
-    int32_t pad;
+    int32_t ragged;    // matrix: 4-wide accesses at element alignment, rows of any length >= 4
 };
 
 // A contiguous range of the tile table served by one launch of the
-// streaming kernel: the matrix tiles of one storage type (4-wide ones
-// first, then one-column ones, which the 4-wide instantiation also serves),
-// then that type's vector tiles.  vec (4, or 1 when the type has no 4-wide
-// matrix tile) selects the kernel instantiation.
+// streaming kernel: the matrix tiles of one storage type (4-wide ones first,
+// then ragged ones, then one-column ones, which the 4-wide instantiation
+// also serves), then that type's vector tiles.  vec (4, or 1 when the type
+// has no 4-wide matrix tile) and ragged (some tile is) select the kernel
+// instantiation.
 struct TileGroup {
     int32_t dtype;
     int32_t vec;
     int64_t begin;
     int64_t count;
+    int32_t ragged;
 };
 
 // One workgroup of the finalisation pass (one launch), T threads.
@@ -136,6 +147,10 @@ struct TileGroup {
 //             power of two that leaves each thread at most kFinLoads
 //             stripes, capped so that an item keeps at least one group.
 //             start is a multiple of 16.
+//   FIN_ROWS_WIDE  256 rows of a matrix with many column blocks (the planner's
+//             rule): lane t of every wave takes rows start + 4t .. + 3, the
+//             waves consecutive ranges of the blocks.  start is a multiple
+//             of 256.
 // An item carries what it needs of its tensor, so that a workgroup's first
 // load is its only descriptor load.
 struct FinItem {

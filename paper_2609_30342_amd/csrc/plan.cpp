@@ -3,7 +3,6 @@
 
 #include <cmath>
 #include <cstdint>
-#include <initializer_list>
 
 namespace rk {
 
@@ -126,18 +125,33 @@ bool grad_fits(const void *g, int32_t dtype, int32_t vec)
 }
 
 // Column blocks of a matrix: kBlockLanes lanes x vec columns each; a narrow
-// last block uses the smallest power-of-two lane count that covers it.
+// last block uses the smallest power-of-two lane count that covers it.  The
+// lanes of ragged rows are shared out evenly over the blocks instead, so that
+// a row one column longer than its blocks (n = 769) does not leave a block of
+// one column, whose tiles would cost as much as full ones; its last block's
+// last lane may hold fewer than vec columns.
 // Tiles are kStreamWaves waves x rpw rows, rpw = base rows per wave, grown
 // for narrow blocks so that every tile has about the same number of
 // accesses.  Returns rpw.
 namespace {
 struct Block { int32_t col0, ncols, llog; };
 
-int matrix_blocks(int64_t n, int32_t vec, int base, std::vector<Block> &blocks)
+int matrix_blocks(int64_t n, int32_t vec, bool ragged, int base, std::vector<Block> &blocks)
 {
     blocks.clear();
     int blog = 0;
     while ((1 << blog) < kBlockLanes) ++blog;
+    if (ragged) {
+        const int64_t all = ceil_div(n, vec);
+        const int64_t nb = ceil_div(all, int64_t(1) << blog), per = ceil_div(all, nb);
+        int llog = 0;
+        while ((int64_t(1) << llog) < per) ++llog;
+        for (int64_t c = 0; c < n; c += per * vec)
+            blocks.push_back({static_cast<int32_t>(c),
+                              static_cast<int32_t>(n - c < per * vec ? n - c : per * vec), llog});
+        const int rpw = base << (blog - llog);
+        return rpw > kMaxRowsPerWave ? kMaxRowsPerWave : rpw;
+    }
     const int64_t lanes = n / vec;
     const int64_t full = lanes >> blog, rem = lanes & ((int64_t(1) << blog) - 1);
     for (int64_t b = 0; b < full; ++b)
@@ -156,8 +170,12 @@ int matrix_blocks(int64_t n, int32_t vec, int base, std::vector<Block> &blocks)
 }  // namespace
 
 rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::string &err,
-                          int rows_per_wave)
+                          int rows_per_wave, bool wide)
 {
+    // Rows of at least one access; shorter ones stay on the one-column path.
+    auto is_ragged = [wide](const rikfad_tensor &T) {
+        return wide && T.n >= kRaggedVec && matrix_vec(T) == 1;
+    };
     if (count < 0 || (count > 0 && !t)) {
         err = "tensor list is NULL or count < 0";
         return RIKFAD_EINVAL;
@@ -193,7 +211,9 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
         for (int64_t i = 0; i < count; ++i) {
             const rikfad_tensor &T = t[i];
             if (T.m == 1 || T.n == 1) continue;
-            const int rpw = matrix_blocks(T.n, matrix_vec(T), kRowsPerWave, blocks);
+            const bool rag = is_ragged(T);
+            const int rpw = matrix_blocks(T.n, rag ? kRaggedVec : matrix_vec(T), rag,
+                                          kRowsPerWave, blocks);
             ntiles += static_cast<int64_t>(blocks.size()) *
                       ceil_div(T.m, int64_t(kStreamWaves) * rpw);
         }
@@ -214,6 +234,7 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
     const int32_t class_dtype[kClasses] = {DT_F32, DT_F32, DT_BF16, DT_BF16};
     const int32_t class_vec[kClasses] = {4, 1, 4, 1};
     std::vector<Tile> mat_tiles[kClasses];
+    std::vector<Tile> ragged_tiles[2];
     std::vector<Tile> vec_tiles[2];
     std::vector<FinItem> col_items;
     for (int64_t i = 0; i < count; ++i) {
@@ -254,7 +275,11 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
         pl.stream_min_bytes += mn * (3 * eb + 8) + 4 * (T.m + T.n); // R, C read only
 
         std::vector<Block> blocks;
-        const int rpw = matrix_blocks(T.n, d.vec, rpw_base, blocks);
+        // d.vec stays 1 for ragged rows: it is what gradients given later
+        // must be aligned to.
+        const bool rag = is_ragged(T);
+        const int32_t vec = rag ? kRaggedVec : d.vec;
+        const int rpw = matrix_blocks(T.n, vec, rag, rpw_base, blocks);
         const int64_t stripe_rows = int64_t(kStreamWaves) * rpw;
         d.ncb = static_cast<int32_t>(blocks.size());
         d.nrs = static_cast<int32_t>(ceil_div(T.m, stripe_rows));
@@ -274,7 +299,14 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
         // narrow tile would land on the odd XCDs.  In runs of 8 stripes such
         // a matrix is therefore ordered block by block, so that all blocks of
         // one stripe lie 8 apart and run on the same XCD.
-        const bool group8 = blocks.back().llog < blocks.front().llog;
+        // So is a matrix whose rows do not start on 128-byte lines: its blocks
+        // meet inside lines, which then stay within one XCD's L2 instead of
+        // being fetched and written back in part by two (streaming kernel,
+        // 16 x 3072 x 1016 bf16: 172 -> 141 us, 16 x 3072 x 1000 fp32: 196 ->
+        // 176 us; rows of whole lines measured alike both ways).
+        const bool lines = (T.n * eb) % 128 == 0 && T.n % 32 == 0 && aligned(T.x, 128) &&
+                           aligned(T.p, 128);
+        const bool group8 = !lines || blocks.back().llog < blocks.front().llog;
         std::vector<std::pair<int32_t, int32_t>> order;     // (stripe, block)
         for (int32_t s0 = 0; s0 < d.nrs; s0 += 8) {
             const int32_t k = d.nrs - s0 < 8 ? d.nrs - s0 : 8;
@@ -299,10 +331,11 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
             tl.cb = b;
             tl.lanes_log2 = blocks[static_cast<size_t>(b)].llog;
             tl.kind = KIND_MATRIX;
-            tl.vec = d.vec;
+            tl.vec = vec;
             tl.dtype = T.dtype;
             tl.rpw = rpw;
-            mat_tiles[cls].push_back(tl);
+            tl.ragged = rag ? 1 : 0;
+            (rag ? ragged_tiles[T.dtype == DT_F32 ? 0 : 1] : mat_tiles[cls]).push_back(tl);
         }
     }
     // Finalisation items (layout.hpp), sized for the set's workgroup: 1024
@@ -317,10 +350,16 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
         const TensorDesc &d = pl.tensors[static_cast<size_t>(i)];
         if (d.kind != KIND_MATRIX) continue;
         // Row items: 4 rows per thread, one partial sum of R per 256 rows.
-        const int64_t rows = 4 * fin_threads;
+        // With many column blocks a thread's chain of dependent rounds of
+        // loads sets the launch's time (768 x 50257: 197 blocks, 50 rounds,
+        // one workgroup), so such matrices get one item per 256 rows whose
+        // waves share the blocks.
+        const bool split = wide && d.ncb > kFinWideBlocks;
+        const int64_t rows = split ? kChunkRows : 4 * fin_threads;
         for (int64_t r0 = 0; r0 < d.m; r0 += rows)
             pl.fin.push_back({d.r, d.m, d.rowpart, d.chunk + r0 / kChunkRows,
-                              static_cast<int32_t>(i), FIN_ROWS, static_cast<int32_t>(r0),
+                              static_cast<int32_t>(i), split ? FIN_ROWS_WIDE : FIN_ROWS,
+                              static_cast<int32_t>(r0),
                               static_cast<int32_t>(d.m - r0 < rows ? d.m - r0 : rows), d.ncb, 0});
         // Column items: S stripe lanes x fin_threads / S threads of 4 columns.
         int slog = 0;
@@ -332,16 +371,21 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
                                  static_cast<int32_t>(d.n - j0 < cols ? d.n - j0 : cols), d.nrs,
                                  slog});
     }
-    // One launch per storage type: its 4-wide matrix tiles, then its
-    // one-column matrix tiles (served by the same launch), then its vector
-    // tiles; the group's width selects the kernel instantiation.
-    auto add_group = [&](int32_t dtype, int32_t vec, std::initializer_list<int> classes,
-                         bool vectors) {
-        TileGroup gr{dtype, vec, static_cast<int64_t>(pl.tiles.size()), 0};
-        for (int cls : classes) {
-            pl.tiles.insert(pl.tiles.end(), mat_tiles[cls].begin(), mat_tiles[cls].end());
-            pl.matrix_tiles += static_cast<int64_t>(mat_tiles[cls].size());
-        }
+    // One launch per storage type: its 4-wide matrix tiles, then its ragged
+    // and its one-column matrix tiles (served by the same launch), then its
+    // vector tiles; the group's width selects the kernel instantiation.
+    auto add_group = [&](int32_t dtype, int32_t vec, int first, bool vectors) {
+        TileGroup gr{dtype, vec, static_cast<int64_t>(pl.tiles.size()), 0, 0};
+        const std::vector<Tile> &rag = ragged_tiles[dtype == DT_F32 ? 0 : 1];
+        auto add = [&](const std::vector<Tile> &tiles) {
+            pl.tiles.insert(pl.tiles.end(), tiles.begin(), tiles.end());
+            pl.matrix_tiles += static_cast<int64_t>(tiles.size());
+        };
+        add(mat_tiles[first]);
+        add(rag);
+        add(mat_tiles[first + 1]);
+        gr.ragged = rag.empty() ? 0 : 1;
+        if (gr.ragged) gr.vec = kRaggedVec;
         if (vectors) {
             const std::vector<Tile> &vt = vec_tiles[dtype == DT_F32 ? 0 : 1];
             pl.tiles.insert(pl.tiles.end(), vt.begin(), vt.end());
@@ -349,8 +393,8 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
         gr.count = static_cast<int64_t>(pl.tiles.size()) - gr.begin;
         if (gr.count > 0) pl.groups.push_back(gr);
     };
-    add_group(DT_F32, mat_tiles[0].empty() ? 1 : 4, {0, 1}, true);
-    add_group(DT_BF16, mat_tiles[2].empty() ? 1 : 4, {2, 3}, true);
+    add_group(DT_F32, mat_tiles[0].empty() ? 1 : 4, 0, true);
+    add_group(DT_BF16, mat_tiles[2].empty() ? 1 : 4, 2, true);
     pl.row_items = static_cast<int64_t>(pl.fin.size());
     pl.fin.insert(pl.fin.end(), col_items.begin(), col_items.end());
     pl.ws_floats = ws;
