@@ -86,14 +86,6 @@ __device__ __forceinline__ int64_t row_off(const Lanes &t, int rl, int64_t n)
     return (t.colok && rl < t.nr ? t.r0 + rl : t.r_any) * n + t.lcol;
 }
 
-// v where keep, else +0, by a bitwise mask: a select on a loaded value can
-// be compiled into a branch around the load, and a load under a branch
-// makes the wave wait for every load it has in flight.
-__device__ __forceinline__ float masked(float v, bool keep)
-{
-    return __uint_as_float(__float_as_uint(v) & (keep ? 0xffffffffu : 0u));
-}
-
 // Row sums of the statistics pass, kRowChunk row loads at a time.  a[u] is
 // this lane's share of the row of load c0 + u (row (c0 + u) * G + seg); the
 // L lanes of a row are combined pairwise by lane bit 0, 1, 2, ... -- the

@@ -213,6 +213,53 @@ template <> struct Raw<uint16_t, 1> {
 
 // ---------------------------------------------------------- reductions
 
+// Lane exchanges in the VALU (moves within 16 lanes, swaps of 16 or 32 lanes):
+// a butterfly of __shfl_xor is a chain of LDS-crossbar round trips, six for
+// every row a wave walks.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kQuadXor1 = 0xb1;     // lane ^ 1 (quad permutation 1 0 3 2)
+constexpr int kQuadXor2 = 0x4e;     // lane ^ 2 (quad permutation 2 3 0 1)
+constexpr int kHalfMirror = 0x141;  // 7 - lane within 8 lanes
+constexpr int kRowMirror = 0x140;   // 15 - lane within 16 lanes
+
+// v plus the value 16 (32) lanes away: swapping the odd 16-lane rows of one
+// copy with the even rows of another (the upper half with the lower) leaves
+// the two addends side by side.
+__device__ __forceinline__ float add_row16(float v)
+{
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
+__device__ __forceinline__ float add_half32(float v)
+{
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
+
+// Sum over each group of 2^llog consecutive lanes; the same bits in all of
+// them.  The mirrors pair lanes whose halves already agree.
+__device__ __forceinline__ float group_sum(float v, int llog)
+{
+    if (llog > 0) v += dpp<kQuadXor1>(v);
+    if (llog > 1) v += dpp<kQuadXor2>(v);
+    if (llog > 2) v += dpp<kHalfMirror>(v);
+    if (llog > 3) v += dpp<kRowMirror>(v);
+    if (llog > 4) v = add_row16(v);
+    if (llog > 5) v = add_half32(v);
+    return v;
+}
+__device__ __forceinline__ float wave_sum(float v) { return group_sum(v, 6); }
+
+// Lane l's value, l the same in every lane.
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
 // Sum of the partial sums of R written by the finalisation pass.  Every
 // wave of every workgroup of a tensor evaluates the same expression in the
 // same order, so all of them obtain the same bits.
@@ -224,6 +271,14 @@ __device__ __forceinline__ float sum_r(const float *__restrict__ part, int count
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) s += __shfl_xor(s, o);
     return s;
+}
+
+// v where keep, else +0, by a bitwise mask: a select on a loaded value can
+// be compiled into a branch around the load, and a load under a branch
+// makes the wave wait for every load it has in flight.
+__device__ __forceinline__ float masked(float v, bool keep)
+{
+    return __uint_as_float(__float_as_uint(v) & (keep ? 0xffffffffu : 0u));
 }
 
 // v - h g and d v with the split coefficients (h = h + h_lo, d = 1 + dm1):

@@ -22,6 +22,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "device.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
@@ -68,7 +70,17 @@ template <> struct RingDepth<uint16_t> { static constexpr int value = kRingBF16;
 // RAG: a ragged row's last lane can hold fewer than V columns.  It then reads
 // the row's last V elements and owns the last V - skip of them; the others
 // are another lane's (or another workgroup's, which may be rewriting them):
-// they are masked out of the sums and not stored.  Against the one-column
+// they are masked out of the sums and not stored.
+//
+// LAT: the form for launches of at most kShortLaunch tiles, which run as long
+// as a few tiles' chains of dependent steps: factors in one round trip, row
+// sums and row factors by VALU lane exchanges instead of the LDS crossbar.
+// Streaming kernel, either form (same box): GPT2-Nano fp32 (1,560 tiles) 42.5
+// -> 40.1 us, TinyViT bf16 (2,340) 44.4 -> 43.3, 64 x 1024^2 fp32 (8,192)
+// 220 -> 217, 256 x 512 6.7 -> 5.4; GPT2-S fp32 (15,275 tiles) 403 -> 414, where
+// the staggered start of the other form pays.
+//
+// Ragged rows against the one-column
 // path that such rows took before (4-byte, bf16 2-byte loads, 64-column
 // blocks): 768 x 50257 and 8 matrices of 769 columns 258 -> 159 us in bf16
 // (finalisation 81 -> 6.4 us, a quarter of the blocks), with the same fp32 set
@@ -76,7 +88,7 @@ template <> struct RingDepth<uint16_t> { static constexpr int value = kRingBF16;
 // TB/s; 4.2-5.0 here) is the 128-byte lines that two blocks share: both
 // fetch them and write them in part.  Plain instead of non-temporal accesses,
 // which could merge in L2, are 2-6% slower in fp32.
-template <typename XT, int V, bool RAG>
+template <typename XT, int V, bool RAG, bool LAT>
 __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
                               const Tile &tile, float *__restrict__ ws,
                               const Coeffs &k, int pending, float *lds)
@@ -105,6 +117,9 @@ __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
     XT *__restrict__ x = static_cast<XT *>(td.x);
     float *__restrict__ p = td.p;
 
+    // A lane outside the block's columns reads the block's first ones.
+    const int64_t lcol = colok ? col : RAG ? min<int64_t>(tile.col0, n - V) : tile.col0;
+
     // The factors are read before the first row load goes out.  Vector
     // loads complete in issue order (one counter per wave), so factor loads
     // issued behind the row loads would hold the first row until the whole
@@ -112,20 +127,39 @@ __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
     // tensor, C, the partial sums of R, R) also staggers when workgroups
     // start streaming, which the memory queues favour: this order measured
     // faster than issuing the rows first, and than batching the factor
-    // loads into one round trip.
-    float cv[V];
+    // loads into one round trip.  In a short launch (LAT) there is no queue to
+    // stagger and each tile's latency shows: there the factor loads are
+    // unconditional and go out together (addresses clamped, values masked).
+    float cv[V], myrate;
+    if constexpr (LAT) {
+        constexpr int CL = 8;
+        const float rraw = gmem(td.r)[lane < nr ? r0 + lane : tile.start];
+        float craw[V], part[CL];
 #pragma unroll
-    for (int i = 0; i < V; ++i) cv[i] = colok ? gmem(td.c)[col + i] : 0.f;
-    const float denom = sum_r(ws + td.chunk, td.nchunk) + k.eps;
-    const float myrate = lane < nr ? row_rate(k.kh, gmem(td.r)[r0 + lane], denom) : 0.f;
+        for (int i = 0; i < V; ++i) craw[i] = gmem(td.c)[lcol + i];
+        const RK_GLOBAL float *pp = gmem(ws) + td.chunk;
+#pragma unroll
+        for (int u = 0; u < CL; ++u) part[u] = pp[min(u * kWave + lane, td.nchunk - 1)];
+        float s = 0.f;
+#pragma unroll
+        for (int u = 0; u < CL; ++u) s += masked(part[u], u * kWave + lane < td.nchunk);
+        for (int i = CL * kWave + lane; i < td.nchunk; i += kWave) s += pp[i];
+        const float denom = wave_sum(s) + k.eps;
+        myrate = lane < nr ? row_rate(k.kh, rraw, denom) : 0.f;
+#pragma unroll
+        for (int i = 0; i < V; ++i) cv[i] = colok ? craw[i] : 0.f;
+    } else {
+#pragma unroll
+        for (int i = 0; i < V; ++i) cv[i] = colok ? gmem(td.c)[col + i] : 0.f;
+        const float denom = sum_r(ws + td.chunk, td.nchunk) + k.eps;
+        myrate = lane < nr ? row_rate(k.kh, gmem(td.r)[r0 + lane], denom) : 0.f;
+    }
 
     // Ring of B row loads: the load of row-load ld + B is issued as soon
     // as row-load ld has been consumed, so a wave keeps up to B 1 KB
     // requests per stream in flight.
     typename Raw<XT, V>::type xr[B], gr[B];
     float qv[B][V];
-    // A lane outside the block's columns reads the block's first ones.
-    const int64_t lcol = colok ? col : RAG ? min<int64_t>(tile.col0, n - V) : tile.col0;
 #pragma unroll
     for (int u = 0; u < B; ++u)
         if (nr > 0)
@@ -143,7 +177,8 @@ __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
             const int ld = ld0 + u;
             const int rl = ld * G + seg;
             const bool ok = colok && rl < nr;
-            const float rate = __shfl(myrate, rl & (kWave - 1));
+            const float rate = LAT && llog == 6 ? lane_value(myrate, ld & (kWave - 1))
+                                                : __shfl(myrate, rl & (kWave - 1));
             float xv[V], gv[V];
             Raw<XT, V>::unpack(xr[u], xv);
             Raw<XT, V>::unpack(gr[u], gv);
@@ -176,10 +211,18 @@ __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
             const int rn = (ld + B) * G + seg;
             if (ld + B < nld)
                 load_row<XT, V>(x, g, p, r0, n, lcol, colok && rn < nr, rn, xr[u], gr[u], qv[u]);
-            for (int o = 1; o < L; o <<= 1) rs += __shfl_xor(rs, o);
-            const int first = ld * G;                 // first row of this load
-            const float v = __shfl(rs, ((lane - first) & (G - 1)) << llog);
-            if (lane >= first && lane < first + G) myrow = v;
+            if (LAT) {
+                rs = group_sum(rs, llog);
+            } else {
+                for (int o = 1; o < L; o <<= 1) rs += __shfl_xor(rs, o);
+            }
+            if (LAT && llog == 6) {                   // one row: every lane has its sum
+                if (lane == ld) myrow = rs;
+            } else {
+                const int first = ld * G;             // first row of this load
+                const float v = __shfl(rs, ((lane - first) & (G - 1)) << llog);
+                if (lane >= first && lane < first + G) myrow = v;
+            }
         }
     }
 
@@ -289,7 +332,7 @@ __device__ void elementwise_tile(const TensorDesc &td, const void *g, const Tile
 // serves, so each carries only the registers its own path needs; vector
 // tiles of the same storage type ride along (element-wise iKFAD).  RAG: the
 // launch has ragged tiles (more registers than the whole-access path).
-template <typename XT, int V, bool RAG>
+template <typename XT, int V, bool RAG, bool LAT>
 __global__ __launch_bounds__(kStreamThreads) void rikfad_stream_kernel(
     const TensorDesc *__restrict__ tensors, const void *const *__restrict__ grads,
     const Tile *__restrict__ tiles, int64_t tile0, int64_t ntile, float *__restrict__ ws,
@@ -306,11 +349,11 @@ __global__ __launch_bounds__(kStreamThreads) void rikfad_stream_kernel(
     // Tensors whose rows break 16-byte alignment ride along in the same
     // launch: ragged tiles, or the one-column path for rows of 2 or 3.
     if (V > 1 && tile.vec == 1)
-        stream_matrix<XT, 1, false>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
+        stream_matrix<XT, 1, false, LAT>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
     else if (RAG && tile.ragged)
-        stream_matrix<XT, V, RAG>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
+        stream_matrix<XT, V, RAG, LAT>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
     else
-        stream_matrix<XT, V, false>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
+        stream_matrix<XT, V, false, LAT>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
 }
 
 // Finalisation (C.2 / C.3 stage 2), one launch of T-thread workgroups.
@@ -783,15 +826,18 @@ hipError_t launch_stream(const TensorDesc *tensors, const void *const *grads, co
             return launch(kernel, grid, block, stream, a, b, tensors, grads, tiles, gr.begin,
                           gr.count, ws, k, pending, flag);
         };
-        hipError_t e;
-        if (gr.dtype == DT_F32)
-            e = gr.ragged     ? go(rikfad_stream_kernel<float, 4, true>)
-                : gr.vec == 4 ? go(rikfad_stream_kernel<float, 4, false>)
-                              : go(rikfad_stream_kernel<float, 1, false>);
-        else
-            e = gr.ragged     ? go(rikfad_stream_kernel<uint16_t, 4, true>)
-                : gr.vec == 4 ? go(rikfad_stream_kernel<uint16_t, 4, false>)
-                              : go(rikfad_stream_kernel<uint16_t, 1, false>);
+        auto form = [&](auto lat) {
+            constexpr bool LAT = decltype(lat)::value;
+            if (gr.dtype == DT_F32)
+                return gr.ragged     ? go(rikfad_stream_kernel<float, 4, true, LAT>)
+                       : gr.vec == 4 ? go(rikfad_stream_kernel<float, 4, false, LAT>)
+                                     : go(rikfad_stream_kernel<float, 1, false, LAT>);
+            return gr.ragged     ? go(rikfad_stream_kernel<uint16_t, 4, true, LAT>)
+                   : gr.vec == 4 ? go(rikfad_stream_kernel<uint16_t, 4, false, LAT>)
+                                 : go(rikfad_stream_kernel<uint16_t, 1, false, LAT>);
+        };
+        const hipError_t e =
+            gr.count <= kShortLaunch ? form(std::true_type{}) : form(std::false_type{});
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
