@@ -23,6 +23,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "adafactor.hpp"
 #include "device.hpp"
 #include "launch.hpp"
@@ -200,8 +202,8 @@ __device__ __forceinline__ float tile_factors(const TensorDesc &td, const Lanes 
 
 // The same factors for the read passes, with every load issued at once:
 // columns from the clamped column lcol, the partial sums of R in batches of
-// kChunkLoads per lane (summed in the order of sum_r: lane, lane + 64, ...,
-// then the butterfly), and R from a clamped row.  Identical values.
+// kChunkLoads per lane (lane, lane + 64, ..., then the wave), and R from a
+// clamped row.
 constexpr int kChunkLoads = 8;
 
 template <int V>
@@ -226,8 +228,7 @@ __device__ __forceinline__ float read_factors(const TensorDesc &td, const Lanes 
 #pragma unroll
         for (int u = 0; u < kChunkLoads; ++u) s += masked(v[u], i0 + u * kWave + t.lane < nch);
     }
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) s += __shfl_xor(s, o);
+    s = wave_sum(s);
     const float inv_s = s > 0.f ? 1.f / s : 0.f;
 #pragma unroll
     for (int i = 0; i < V; ++i) fc[i] = t.colok ? col_factor(cv[i]) : 0.f;
@@ -350,8 +351,13 @@ struct StatsVec {
     }
 };
 
+// With more than 80 scalar registers a compute unit holds 3 of its workgroups
+// instead of 4 (82: GPT2-S bf16 47.3 us, 80: 44.0; fp32 the same).
+constexpr int kStatsSgprs = 80;
+
 template <typename XT, int V, bool RAG, bool X2>
-__global__ __launch_bounds__(kStreamThreads) void adafm_stats_kernel(
+__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_num_sgpr(kStatsSgprs)))
+void adafm_stats_kernel(
     const TensorDesc *__restrict__ tensors, const void *const *__restrict__ grads,
     const Tile *__restrict__ tiles, int64_t tile0, float *__restrict__ ws,
     float *__restrict__ tilepart, AdaCoeffs k)
@@ -387,7 +393,17 @@ __global__ __launch_bounds__(kStreamThreads) void adafm_stats_kernel(
 // Sum of U^2 over one matrix tile (this lane's share), in batches of row
 // loads as in the statistics pass.  The first batch goes out before the
 // factor loads, so their round trips overlap.
-template <typename XT, int V, bool RAG>
+//
+// KEEP: the update pass reads this gradient again, in the opposite order, so
+// the last tiles of this pass (as much as the 256 MB memory-side cache holds
+// beside the update's other streams) load it without the non-temporal hint.
+// The loads themselves are slower (GPT2-S fp32, half of 498 MB: 73 -> 77 us),
+// the update pass gains more: fp32 414 -> 390 us, bf16 (all 249 MB) 278 ->
+// 250 us; it is bound by HBM reads and writes together, and what comes from
+// the cache leaves HBM to the rest.  Keeping it in the statistics pass too
+// made that pass 10% slower for nothing: read-only passes go no faster from
+// the cache.
+template <typename XT, int V, bool RAG, bool KEEP>
 __device__ float rms_matrix(const TensorDesc &td, const XT *__restrict__ g, const Tile &tile,
                             const float *__restrict__ ws)
 {
@@ -397,8 +413,10 @@ __device__ float rms_matrix(const TensorDesc &td, const XT *__restrict__ g, cons
     float u2 = 0.f;
     auto issue = [&](int ld0) {
 #pragma unroll
-        for (int u = 0; u < B; ++u)
-            gr[u] = Raw<XT, V>::load(g + row_off(t, (ld0 + u) * t.G + t.seg, td.n));
+        for (int u = 0; u < B; ++u) {
+            const XT *q = g + row_off(t, (ld0 + u) * t.G + t.seg, td.n);
+            gr[u] = KEEP ? Raw<XT, V>::load_kept(q) : Raw<XT, V>::load(q);
+        }
     };
     issue(0);
     float fc[V];
@@ -433,7 +451,7 @@ template <typename XT, int V, bool RAG>
 __global__ __launch_bounds__(kStreamThreads) void adafm_rms_kernel(
     const TensorDesc *__restrict__ tensors, const void *const *__restrict__ grads,
     const Tile *__restrict__ tiles, int64_t tile0, const float *__restrict__ ws,
-    float *__restrict__ tilepart)
+    float *__restrict__ tilepart, int64_t keep_from)
 {
     __shared__ float red[2 * kStreamWaves];
     const int64_t ti = tile0 + blockIdx.x;
@@ -441,15 +459,32 @@ __global__ __launch_bounds__(kStreamThreads) void adafm_rms_kernel(
     if (tile.kind == KIND_VECTOR) return;   // vector sums are complete after pass 1
     const TensorDesc td = tensors[tile.tensor];
     const XT *__restrict__ g = static_cast<const XT *>(grads[tile.tensor]);
-    float u2 = V > 1 && tile.vec == 1 ? rms_matrix<XT, 1, false>(td, g, tile, ws)
-               : RAG && tile.ragged   ? rms_matrix<XT, V, RAG>(td, g, tile, ws)
-                                      : rms_matrix<XT, V, false>(td, g, tile, ws);
+    auto sum = [&](auto keep) {
+        constexpr bool KEEP = decltype(keep)::value;
+        return V > 1 && tile.vec == 1 ? rms_matrix<XT, 1, false, KEEP>(td, g, tile, ws)
+               : RAG && tile.ragged   ? rms_matrix<XT, V, RAG, KEEP>(td, g, tile, ws)
+                                      : rms_matrix<XT, V, false, KEEP>(td, g, tile, ws);
+    };
+    float u2 = ti >= keep_from ? sum(std::true_type{}) : sum(std::false_type{});
     float zero = 0.f;
     block_sum2<kStreamWaves>(u2, zero, red);
     if (threadIdx.x == 0) gmem(tilepart)[2 * ti] = u2;
 }
 
 // ----------------------------------------------------------------- scale
+
+// s = step / max(1, RMS(U) / clip) of a tensor from its sums of U^2 and X^2.
+__device__ __forceinline__ float tensor_scale(float u2, float x2, int64_t elems,
+                                              const AdaCoeffs &k)
+{
+    const double el = static_cast<double>(elems);
+    const double rms_u = sqrt(static_cast<double>(u2) / el);
+    const double rms_x = sqrt(static_cast<double>(x2) / el);
+    double step = k.h;
+    if (k.scale) step *= rms_x > k.eps2 ? rms_x : static_cast<double>(k.eps2);
+    const double div = (k.clip > 0.f && rms_u / k.clip > 1.0) ? rms_u / k.clip : 1.0;
+    return static_cast<float>(step / div);
+}
 
 __global__ __launch_bounds__(kThreads) void adafm_scale_kernel(
     const TensorRange *__restrict__ ranges, const float *__restrict__ tilepart,
@@ -463,15 +498,36 @@ __global__ __launch_bounds__(kThreads) void adafm_scale_kernel(
         x2 += gmem(tilepart)[2 * (rg.tile0 + q) + 1];
     }
     block_sum2<kThreads / kWave>(u2, x2, red);
-    if (threadIdx.x == 0) {
-        const double el = static_cast<double>(rg.elems);
-        const double rms_u = sqrt(static_cast<double>(u2) / el);
-        const double rms_x = sqrt(static_cast<double>(x2) / el);
-        double step = k.h;
-        if (k.scale) step *= rms_x > k.eps2 ? rms_x : static_cast<double>(k.eps2);
-        const double div = (k.clip > 0.f && rms_u / k.clip > 1.0) ? rms_u / k.clip : 1.0;
-        gmem(scales)[blockIdx.x] = static_cast<float>(step / div);
+    if (threadIdx.x == 0) gmem(scales)[blockIdx.x] = tensor_scale(u2, x2, rg.elems, k);
+}
+
+// The same in every wave that needs it, for sets whose tensors all have at
+// most kFoldTiles tiles: the update pass of a short launch then does without
+// the scale launch before it (GPT2-Nano bf16 with parameter scaling: 54.9 ->
+// 52.9 us per step; 100 matrices of 64 x 64: 19.7 -> 16.8).  The scale
+// kernel's order of additions -- 64 tiles in its tree, these sums in order --
+// so the same bits.
+__device__ __forceinline__ float fold_scale(const TensorRange &rg,
+                                            const float *__restrict__ tilepart, const AdaCoeffs &k)
+{
+    constexpr int N = kFoldTiles / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    const RK_GLOBAL f32x2 *part = reinterpret_cast<const RK_GLOBAL f32x2 *>(gmem(tilepart)) + rg.tile0;
+    const int n = static_cast<int>(rg.ntile);
+    f32x2 v[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] = part[min(lane + u * kWave, n - 1)];
+    static_assert(kFoldTiles <= kThreads, "one tile per thread of the scale kernel");
+    float u2 = 0.f, x2 = 0.f;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        if (u > 0 && u * kWave >= n) break;
+        const float su = wave_sum(masked(v[u].x, lane + u * kWave < n));
+        const float sx = wave_sum(masked(v[u].y, lane + u * kWave < n));
+        u2 = u == 0 ? su : u2 + su;
+        x2 = u == 0 ? sx : x2 + sx;
     }
+    return tensor_scale(u2, x2, rg.elems, k);
 }
 
 // ---------------------------------------------------------------- pass 3
@@ -482,7 +538,7 @@ __global__ __launch_bounds__(kThreads) void adafm_scale_kernel(
 template <typename XT> struct UpdateRing { static constexpr int value = kRingF32; };
 template <> struct UpdateRing<uint16_t> { static constexpr int value = kRingBF16; };
 
-template <typename XT, int V, bool RAG>
+template <typename XT, int V, bool RAG, bool FOLD>
 __device__ void update_matrix(const TensorDesc &td, const XT *__restrict__ g, const Tile &tile,
                               const float *__restrict__ ws, float s, const AdaCoeffs &k)
 {
@@ -494,7 +550,7 @@ __device__ void update_matrix(const TensorDesc &td, const XT *__restrict__ g, co
     typename Raw<XT, V>::type gr[B], xr[B];
     float mv[B][V];
     float fc[V];
-    const float myfr = tile_factors<V>(td, t, ws, fc);
+    const float myfr = FOLD ? read_factors<V>(td, t, ws, fc) : tile_factors<V>(td, t, ws, fc);
     if (t.nld > 0) {
 #pragma unroll
         for (int u = 0; u < B; ++u) {
@@ -567,24 +623,26 @@ struct UpdateVec {
     }
 };
 
-template <typename XT, int V, bool RAG>
+// scales: one per tensor, or with FOLD the tile sums to fold.
+template <typename XT, int V, bool RAG, bool FOLD>
 __global__ __launch_bounds__(kStreamThreads) void adafm_update_kernel(
     const TensorDesc *__restrict__ tensors, const void *const *__restrict__ grads,
     const Tile *__restrict__ tiles, int64_t tile0, const float *__restrict__ ws,
-    const float *__restrict__ scales, AdaCoeffs k)
+    const float *__restrict__ scales, const TensorRange *__restrict__ ranges, AdaCoeffs k)
 {
-    const Tile tile = tiles[tile0 + blockIdx.x];
+    // From the last tile to the first: the RMS pass read those last.
+    const Tile tile = tiles[tile0 + gridDim.x - 1 - blockIdx.x];
     const TensorDesc td = tensors[tile.tensor];
     const XT *g = static_cast<const XT *>(grads[tile.tensor]);
-    const float s = gmem(scales)[tile.tensor];
+    const float s = FOLD ? fold_scale(ranges[tile.tensor], scales, k) : gmem(scales)[tile.tensor];
     if (tile.kind == KIND_VECTOR) {
         UpdateVec<XT> op{g, static_cast<XT *>(td.x), td.p, td.xi, s, k};
         flat_tile(tile, op);
         return;
     }
-    if (V > 1 && tile.vec == 1) update_matrix<XT, 1, false>(td, g, tile, ws, s, k);
-    else if (RAG && tile.ragged) update_matrix<XT, V, RAG>(td, g, tile, ws, s, k);
-    else update_matrix<XT, V, false>(td, g, tile, ws, s, k);
+    if (V > 1 && tile.vec == 1) update_matrix<XT, 1, false, FOLD>(td, g, tile, ws, s, k);
+    else if (RAG && tile.ragged) update_matrix<XT, V, RAG, FOLD>(td, g, tile, ws, s, k);
+    else update_matrix<XT, V, false, FOLD>(td, g, tile, ws, s, k);
 }
 
 // Kernel instantiation for a tile group's (storage type, width, ragged
@@ -606,9 +664,9 @@ F pick(const TileGroup &gr, Pick p)
 typedef void (*StatsFn)(const TensorDesc *, const void *const *, const Tile *, int64_t, float *,
                         float *, AdaCoeffs);
 typedef void (*RmsFn)(const TensorDesc *, const void *const *, const Tile *, int64_t,
-                      const float *, float *);
+                      const float *, float *, int64_t);
 typedef void (*UpdateFn)(const TensorDesc *, const void *const *, const Tile *, int64_t,
-                         const float *, const float *, AdaCoeffs);
+                         const float *, const float *, const TensorRange *, AdaCoeffs);
 
 template <bool X2> struct PickStats {
     template <typename XT, int V, bool RAG> StatsFn get() const
@@ -619,10 +677,10 @@ template <bool X2> struct PickStats {
 struct PickRms {
     template <typename XT, int V, bool RAG> RmsFn get() const { return adafm_rms_kernel<XT, V, RAG>; }
 };
-struct PickUpdate {
+template <bool FOLD> struct PickUpdate {
     template <typename XT, int V, bool RAG> UpdateFn get() const
     {
-        return adafm_update_kernel<XT, V, RAG>;
+        return adafm_update_kernel<XT, V, RAG, FOLD>;
     }
 };
 
@@ -651,8 +709,8 @@ hipError_t launch_adafm_stats(const TensorDesc *tensors, const void *const *grad
 
 hipError_t launch_adafm_rms(const TensorDesc *tensors, const void *const *grads,
                             const Tile *tiles, const TileGroup *groups, int ngroups,
-                            const float *ws, float *tilepart, hipStream_t stream,
-                            hipEvent_t start, hipEvent_t stop)
+                            const float *ws, float *tilepart, int64_t keep_from,
+                            hipStream_t stream, hipEvent_t start, hipEvent_t stop)
 {
     const int last = last_group(groups, ngroups);
     for (int q = 0; q < ngroups; ++q) {
@@ -663,7 +721,7 @@ hipError_t launch_adafm_rms(const TensorDesc *tensors, const void *const *grads,
         start = nullptr;
         const hipError_t e = launch(fn, dim3(static_cast<uint32_t>(gr.count)),
                                     dim3(kStreamThreads), stream, a, b, tensors, grads, tiles,
-                                    gr.begin, ws, tilepart);
+                                    gr.begin, ws, tilepart, keep_from);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -680,19 +738,25 @@ hipError_t launch_adafm_scale(const TensorRange *ranges, int64_t ntensors, const
 
 hipError_t launch_adafm_update(const TensorDesc *tensors, const void *const *grads,
                                const Tile *tiles, const TileGroup *groups, int ngroups,
-                               const float *ws, const float *scales, const AdaCoeffs &k,
-                               hipStream_t stream, hipEvent_t start, hipEvent_t stop)
+                               const float *ws, const float *scales, const TensorRange *ranges,
+                               const AdaCoeffs &k, hipStream_t stream, hipEvent_t start,
+                               hipEvent_t stop)
 {
-    const int last = last_group(groups, ngroups);
-    for (int q = 0; q < ngroups; ++q) {
+    // Groups, too, from the last to the first: `stop` goes on the first one
+    // with tiles.
+    int first = -1;
+    for (int q = ngroups - 1; q >= 0; --q)
+        if (groups[q].count > 0) first = q;
+    for (int q = ngroups - 1; q >= 0; --q) {
         const TileGroup &gr = groups[q];
         if (gr.count <= 0) continue;
-        const UpdateFn fn = pick<UpdateFn>(gr, PickUpdate());
-        hipEvent_t a = start, b = q == last ? stop : nullptr;
+        const UpdateFn fn = ranges ? pick<UpdateFn>(gr, PickUpdate<true>())
+                                   : pick<UpdateFn>(gr, PickUpdate<false>());
+        hipEvent_t a = start, b = q == first ? stop : nullptr;
         start = nullptr;
         const hipError_t e = launch(fn, dim3(static_cast<uint32_t>(gr.count)),
                                     dim3(kStreamThreads), stream, a, b, tensors, grads, tiles,
-                                    gr.begin, ws, scales, k);
+                                    gr.begin, ws, scales, ranges, k);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -203,6 +203,12 @@ constexpr int kUpdateRowsPerWave = 3;   // Adafactor-m update pass (see adafm_ct
 // the chip.
 constexpr int kReadRowsPerWave = RK_ADA_READ_ROWS;
 constexpr int64_t kReadMinTiles = 512;
+// Gradient bytes that the RMS pass leaves in the 256 MB memory-side cache for
+// the update pass (adafactor.hip).  GPT2-S fp32 (498 MB of gradients), both
+// passes: none kept 487 us, 128 MB 485, 192 MB 476, 224 MB 470, 256 and 288
+// MB 467.  Eight 4096 x 11008 bf16 matrices (721 MB) measured the same with
+// and without, so beyond twice the cache nothing is kept.
+constexpr int64_t kKeptGradBytes = int64_t(256) << 20;
 
 struct adafm_ctx {
     rk::Plan plan;
@@ -217,6 +223,8 @@ struct adafm_ctx {
     float *scales = nullptr;                // 1 per tensor
     std::vector<const void *> grads_host;
     int64_t min_bytes = 0, update_bytes = 0;
+    bool fold_scale = false;                // the update pass folds the tile sums itself
+    int64_t keep_from = 0;                  // first tile whose gradient the RMS pass keeps cached
     // The update pass has no reductions, so it runs over a tile table of its
     // own with fewer rows per wave (3 against 4: 1.5-3% faster on GPT2-S);
     // tensor descriptors, gradients and workspace are the plan's.
@@ -653,6 +661,27 @@ static rikfad_status adafm_layout(adafm_ctx *ctx)
             return fail(RIKFAD_EINVAL, "internal: tiles of a tensor are not contiguous");
         r.ntile += 1;
     }
+    // Short launches do without the scale launch.
+    int64_t upd_tiles = 0;
+    for (const rk::TileGroup &gr : ctx->upd_groups) upd_tiles += gr.count;
+    ctx->fold_scale = upd_tiles <= rk::kShortLaunch;
+    for (const rk::TensorRange &r : ctx->ranges)
+        ctx->fold_scale = ctx->fold_scale && r.ntile <= rk::kFoldTiles;
+    // The table's last tiles, up to the memory-side cache's size in gradient
+    // bytes; none where the gradients are more than twice that.
+    auto grad_bytes = [](const rk::Tile &tl) {
+        return tl.kind == rk::KIND_MATRIX
+                   ? int64_t(tl.count) * tl.ncols * (tl.dtype == rk::DT_BF16 ? 2 : 4)
+                   : int64_t(0);
+    };
+    int64_t kept = 0, all = 0;
+    for (const rk::Tile &tl : pl.tiles) all += grad_bytes(tl);
+    ctx->keep_from = static_cast<int64_t>(pl.tiles.size());
+    for (size_t q = pl.tiles.size(); q-- > 0 && all <= 2 * kKeptGradBytes;) {
+        kept += grad_bytes(pl.tiles[q]);
+        if (kept > kKeptGradBytes) break;
+        ctx->keep_from = static_cast<int64_t>(q);
+    }
     const int64_t sc = ctx->hp.scale_parameter ? 1 : 0, cl = ctx->hp.clip_threshold > 0 ? 1 : 0;
     ctx->min_bytes = ctx->update_bytes = 0;
     for (size_t i = 0; i < nt; ++i) {
@@ -759,18 +788,24 @@ rikfad_status adafm_step(adafm_ctx *ctx, void *stream_)
     if (ctx->hp.clip_threshold > 0 && pl.matrix_tiles > 0) {
         if ((s = tm.phase(2, &t0, &t1)) != RIKFAD_OK) return s;
         e = rk::launch_adafm_rms(ctx->dev.tensors, ctx->dev.grads, ctx->dev.tiles,
-                                 pl.groups.data(), ng, ctx->dev.ws, ctx->tilepart, stream, t0,
-                                 t1);
+                                 pl.groups.data(), ng, ctx->dev.ws, ctx->tilepart,
+                                 ctx->keep_from, stream, t0, t1);
         if (e != hipSuccess) return hip_fail(e, "launch adafm rms kernel");
     }
-    if ((s = tm.phase(3, &t0, &t1)) != RIKFAD_OK) return s;
-    e = rk::launch_adafm_scale(ctx->ranges_dev, static_cast<int64_t>(pl.tensors.size()),
-                               ctx->tilepart, ctx->scales, k, stream, t0, t1);
-    if (e != hipSuccess) return hip_fail(e, "launch adafm scale kernel");
+    // A timed step launches the scale kernel also where untimed ones fold it
+    // into the update pass (the same bits), so that its time is its own.
+    const bool fold = ctx->fold_scale && !tm.on;
+    if (!fold) {
+        if ((s = tm.phase(3, &t0, &t1)) != RIKFAD_OK) return s;
+        e = rk::launch_adafm_scale(ctx->ranges_dev, static_cast<int64_t>(pl.tensors.size()),
+                                   ctx->tilepart, ctx->scales, k, stream, t0, t1);
+        if (e != hipSuccess) return hip_fail(e, "launch adafm scale kernel");
+    }
     if ((s = tm.phase(4, &t0, &t1)) != RIKFAD_OK) return s;
     e = rk::launch_adafm_update(ctx->dev.tensors, ctx->dev.grads, ctx->upd_tiles,
                                 ctx->upd_groups.data(), static_cast<int>(ctx->upd_groups.size()),
-                                ctx->dev.ws, ctx->scales, k, stream, t0, t1);
+                                ctx->dev.ws, fold ? ctx->tilepart : ctx->scales,
+                                fold ? ctx->ranges_dev : nullptr, k, stream, t0, t1);
     if (e != hipSuccess) return hip_fail(e, "launch adafm update kernel");
     tm.end_step();
     ctx->steps = t;

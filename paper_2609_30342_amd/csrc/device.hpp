@@ -46,6 +46,7 @@ __device__ __forceinline__ void stg(T *q, T v)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // The same, at element alignment: rows of any length start at any element.
 // gfx950 takes them as the same single 16-byte (8-byte) accesses, so the
@@ -168,11 +169,16 @@ template <> struct Io<uint16_t, 1> {
 };
 
 // Raw<T, V>: the V elements of one lane access as loaded (packed bf16 stays
-// packed in registers until it is used).
+// packed in registers until it is used).  load_kept is a plain load, for data
+// that a later kernel reads again.
 template <typename T, int V> struct Raw;
 
 template <> struct Raw<float, 4> {
     typedef f32x4 type;
+    static __device__ __forceinline__ type load_kept(const float *q)
+    {
+        return *(const RK_GLOBAL f32x4e *)q;
+    }
     static __device__ __forceinline__ type load(const float *q)
     {
         return ldg4(q);
@@ -185,12 +191,17 @@ template <> struct Raw<float, 4> {
 
 template <> struct Raw<float, 1> {
     typedef float type;
+    static __device__ __forceinline__ type load_kept(const float *q) { return *gmem(q); }
     static __device__ __forceinline__ type load(const float *q) { return ldg(q); }
     static __device__ __forceinline__ void unpack(const type &v, float (&o)[1]) { o[0] = v; }
 };
 
 template <> struct Raw<uint16_t, 4> {
     typedef u32x2 type;
+    static __device__ __forceinline__ type load_kept(const uint16_t *q)
+    {
+        return *(const RK_GLOBAL u32x2e *)q;
+    }
     static __device__ __forceinline__ type load(const uint16_t *q)
     {
         return ldg4(q);
@@ -204,6 +215,7 @@ template <> struct Raw<uint16_t, 4> {
 
 template <> struct Raw<uint16_t, 1> {
     typedef uint16_t type;
+    static __device__ __forceinline__ type load_kept(const uint16_t *q) { return *gmem(q); }
     static __device__ __forceinline__ type load(const uint16_t *q) { return ldg(q); }
     static __device__ __forceinline__ void unpack(const type &v, float (&o)[1])
     {

@@ -198,6 +198,9 @@ struct AdaCoeffs {
     int32_t pad;
 };
 
+// Most tiles of a tensor whose sums the Adafactor-m update pass folds itself.
+constexpr int kFoldTiles = 256;
+
 // Tiles of one tensor in the tile table (they are contiguous).
 struct TensorRange {
     int64_t tile0;
