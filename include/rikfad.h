@@ -135,9 +135,9 @@ rikfad_status rikfad_create(const rikfad_tensor *tensors, int64_t count,
  * while every step goes through it.  rikfad_sync_momentum,
  * rikfad_set_hparams, rikfad_state_changed and rikfad_step_grads change
  * that state or the gradient table, so they do not belong between replays
- * of one graph.  rikfad_step_grads with changed pointers copies the new
- * table from host memory and may wait for an earlier copy, so it must not
- * be captured. */
+ * of one graph.  rikfad_step_grads with changed pointers writes the new table
+ * first (above 512 tensors by a copy from host memory, which may wait for an
+ * earlier one), so it must not be captured. */
 rikfad_status rikfad_step(rikfad_ctx *ctx, void *stream);
 
 /* As rikfad_step, with new gradient pointers grads[0..count-1] (same shapes,

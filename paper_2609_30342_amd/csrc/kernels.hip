@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device.hpp"
@@ -808,7 +809,30 @@ __global__ __launch_bounds__(kThreads) void probe_write_kernel(u32x4 *__restrict
     }
 }
 
+// ------------------------------------------------------ gradient table
+
+__global__ __launch_bounds__(kGradChunk) void set_grads_kernel(const void **__restrict__ grads,
+                                                               GradChunk chunk, int count)
+{
+    const int i = threadIdx.x;
+    if (i < count) gmem(grads)[i] = chunk.p[i];
+}
+
 // ------------------------------------------------------------- launchers
+
+hipError_t launch_set_grads(const void **grads, const void *const *src, int64_t count,
+                            hipStream_t stream)
+{
+    for (int64_t i = 0; i < count; i += kGradChunk) {
+        GradChunk c = {};
+        const int n = static_cast<int>(std::min<int64_t>(kGradChunk, count - i));
+        std::copy(src + i, src + i + n, c.p);
+        hipLaunchKernelGGL(set_grads_kernel, dim3(1), dim3(kGradChunk), 0, stream, grads + i, c, n);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 hipError_t launch_stream(const TensorDesc *tensors, const void *const *grads, const Tile *tiles,
                          const TileGroup *groups, int ngroups, float *ws, const Coeffs &k,

@@ -29,6 +29,11 @@ hipError_t launch_apply(const TensorDesc *tensors, const Tile *tiles, const Tile
                         int ngroups, const float *ws, const Coeffs &k, hipStream_t stream,
                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 
+// Writes count gradient pointers to the device table, in launches of
+// kGradChunk pointers that carry them as arguments.
+hipError_t launch_set_grads(const void **grads, const void *const *src, int64_t count,
+                            hipStream_t stream);
+
 // Full-tensor element-wise iKFAD.
 hipError_t launch_ikfad(const TensorDesc *tensors, const void *const *grads, const Tile *tiles,
                         int64_t ntiles, const Coeffs &k, int *flag, hipStream_t stream,

@@ -108,6 +108,12 @@ struct TensorDesc {
     int32_t kind, vec;
 };
 
+// Gradient pointers handed to a kernel by value (2 KB of its arguments).
+constexpr int kGradChunk = 256;
+struct GradChunk {
+    const void *p[kGradChunk];
+};
+
 // One workgroup of the streaming pass.
 struct Tile {
     int64_t start;     // matrix: first row; vector: first element
