@@ -67,7 +67,6 @@ __device__ __forceinline__ void load_row(const XT *x, const XT *g, const float *
 template <typename XT> struct RingDepth { static constexpr int value = kRingF32; };
 template <> struct RingDepth<uint16_t> { static constexpr int value = kRingBF16; };
 
-//
 // RAG: a ragged row's last lane can hold fewer than V columns.  It then reads
 // the row's last V elements and owns the last V - skip of them; the others
 // are another lane's (or another workgroup's, which may be rewriting them):
@@ -81,14 +80,13 @@ template <> struct RingDepth<uint16_t> { static constexpr int value = kRingBF16;
 // 220 -> 217, 256 x 512 6.7 -> 5.4; GPT2-S fp32 (15,275 tiles) 403 -> 414, where
 // the staggered start of the other form pays.
 //
-// Ragged rows against the one-column
-// path that such rows took before (4-byte, bf16 2-byte loads, 64-column
-// blocks): 768 x 50257 and 8 matrices of 769 columns 258 -> 159 us in bf16
-// (finalisation 81 -> 6.4 us, a quarter of the blocks), with the same fp32 set
-// 336 -> 223 us per step.  What is left against rows of whole lines (5.6
-// TB/s; 4.2-5.0 here) is the 128-byte lines that two blocks share: both
-// fetch them and write them in part.  Plain instead of non-temporal accesses,
-// which could merge in L2, are 2-6% slower in fp32.
+// Ragged rows against the one-column path that such rows took before (4-byte,
+// in bf16 2-byte loads, 64-column blocks): 768 x 50257 and 8 matrices of 769
+// columns in bf16 258 -> 159 us (finalisation 81 -> 6.4 us, a quarter of the
+// blocks), the same set in fp32 336 -> 223 us per step.  What is left against
+// rows of whole lines (5.6 TB/s; 4.2-5.0 here) is the 128-byte lines that two
+// blocks share: both fetch them and write them in part.  Plain instead of
+// non-temporal accesses, which could merge in L2, are 2-6% slower in fp32.
 template <typename XT, int V, bool RAG, bool LAT>
 __device__ void stream_matrix(const TensorDesc &td, const XT *__restrict__ g,
                               const Tile &tile, float *__restrict__ ws,
@@ -362,7 +360,10 @@ __global__ __launch_bounds__(kStreamThreads) void rikfad_stream_kernel(
 // bytes at a time.  Row items: thread t owns rows start + 4t .. + 3, sums
 // their column-block partials in block order and updates R; the 256 rows of
 // a wave give one partial sum of R (each thread's four new values in order,
-// then a butterfly across the wave).  Column items: thread t owns columns
+// then a butterfly across the wave).  Wide row items (more than
+// kFinWideBlocks column blocks) cover 256 rows whose blocks the waves share
+// (8 x 4096 x 11008 with Adafactor-m's tiles, 43 blocks: 7.7 -> 5.2 us).
+// Column items: thread t owns columns
 // 4(t mod 4) .. + 3 of a 16-column group and stripe lane q of S; it sums
 // stripes q, q + S, q + 2S, ... in that order (kFinLoads loads in flight;
 // the lanes of a wave read consecutive stripes of a group, one contiguous
