@@ -78,7 +78,9 @@ template <> struct RingDepth<uint16_t> { static constexpr int value = kRingBF16;
 // Streaming kernel, either form (same box): GPT2-Nano fp32 (1,560 tiles) 42.5
 // -> 40.1 us, TinyViT bf16 (2,340) 44.4 -> 43.3, 64 x 1024^2 fp32 (8,192)
 // 220 -> 217, 256 x 512 6.7 -> 5.4; GPT2-S fp32 (15,275 tiles) 403 -> 414, where
-// the staggered start of the other form pays.
+// the staggered start of the other form pays.  Launches with ragged tiles cross
+// over earlier (8 x 3072 x 769 bf16, 3,072 tiles: 60.2 -> 59.6; a set of 6,600:
+// 159 -> 162).
 //
 // Ragged rows against the one-column path that such rows took before (4-byte,
 // in bf16 2-byte loads, 64-column blocks): 768 x 50257 and 8 matrices of 769
@@ -862,7 +864,8 @@ hipError_t launch_stream(const TensorDesc *tensors, const void *const *grads, co
                                  : go(rikfad_stream_kernel<uint16_t, 1, false, LAT>);
         };
         const hipError_t e =
-            gr.count <= kShortLaunch ? form(std::true_type{}) : form(std::false_type{});
+            gr.count <= (gr.ragged ? kShortRagged : kShortLaunch) ? form(std::true_type{})
+                                                                  : form(std::false_type{});
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
