@@ -668,13 +668,18 @@ constexpr int64_t kScratchWords = int64_t(1) << 21;    // static workspace: 16 M
 constexpr int64_t kOnePassMaxCols = 16384;  // 16 waves x 4 16-byte loads per lane
 constexpr int kOnePassMaxBlocks = 256;      // compute units: one round of 16-wave workgroups
 
-// Workspace of one report, in doubles, and the launch geometry it implies.
+// Launch geometry of one report and its workspace: words doubles, and the
+// place of every buffer in it, so that the size cannot differ from the layout.
 struct ReportShape {
     int64_t stripe, nstripes, ncb, nerr, nfold, nstat, words;
     // one-pass report: row length of the partial sums, workgroups and rows
-    // per workgroup (0: two passes per iteration)
+    // per workgroup (nblk 0: two passes per iteration)
     int64_t stride;
     int nblk, rows;
+    // Buffers: R and u (two-pass form only), C, v, column partial sums, fold
+    // partials of C and of v, error partials, norm partials (vector statistics
+    // in the two-pass form), the six results
+    int64_t r, u, c, v, cpart, cfold, vfold, epart, spart, res;
 };
 
 ReportShape report_shape(int64_t m, int64_t n)
@@ -692,21 +697,17 @@ ReportShape report_shape(int64_t m, int64_t n)
     s.nfold = (n + kFoldCols - 1) / kFoldCols;
     const int64_t mk = m > n ? m : n;
     s.nstat = (mk + kStatChunk - 1) / kStatChunk;
-    // r m, c n, u m, v n, column partials, error partials 2*nerr, fold
-    // partials (C and v), statistics partials 2*nstat, results 2 (R), 2 (u),
-    // 2 (errors).  Where rows are 1024 columns at most, the column partials
-    // are counted as one row per 256 rows of xi, and the fold partials as one
-    // pair per 4 columns.
-    const int64_t nparts = n <= 1024 ? (m + 255) / 256 : s.nstripes;
-    s.words = m + n + m + n + nparts * n + 2 * s.nerr + 4 * ((n + 3) / 4) + 2 * s.nstat + 6;
+    int64_t end = 0;
+    auto take = [&end](int64_t count) {
+        const int64_t at = end;
+        end += count;
+        return at;
+    };
     s.stride = (n + 3) / 4 * 4;
     s.nblk = s.rows = 0;
     if (n >= 4 && n <= kOnePassMaxCols) {
-        // c, v, fold partials of both, error and norm partials, results; the
-        // rest of the static workspace bounds the partial sums (only above
-        // 8000 columns: 185 workgroups of 4096 x 11008 still take the
-        // memory-side cache's rate).  words covers both forms, so whether a
-        // tensor fits the static workspace does not depend on the form.
+        // The rest of the static workspace bounds the partial sums (only
+        // above 8000 columns: 187 workgroups for 4096 x 11008).
         const int64_t fixed = 2 * s.stride + 4 * s.nfold + 6 + 16;
         int64_t most = (kScratchWords - fixed) / (s.stride + 4);
         if (most > kOnePassMaxBlocks) most = kOnePassMaxBlocks;
@@ -720,9 +721,34 @@ ReportShape report_shape(int64_t m, int64_t n)
         if (rows < least) rows = least;
         s.rows = static_cast<int>(rows);
         s.nblk = static_cast<int>((m + rows - 1) / rows);
-        const int64_t need = fixed + s.nblk * (s.stride + 4);
-        if (need > s.words) s.words = need;
+        s.r = s.u = -1;
+        s.c = take(s.stride);
+        s.v = take(s.stride);
+        s.cpart = take(s.nblk * s.stride);
+        s.cfold = take(2 * s.nfold);
+        s.vfold = take(2 * s.nfold);
+        s.epart = take(2 * s.nblk);
+        s.spart = take(2 * s.nblk);
+    } else {
+        s.r = take(m);
+        s.c = take(n);
+        s.u = take(m);
+        s.v = take(n);
+        s.cpart = take(s.nstripes * n);
+        s.epart = take(2 * s.nerr);
+        s.cfold = take(2 * s.nfold);
+        s.vfold = take(2 * s.nfold);
+        s.spart = take(2 * s.nstat);
     }
+    s.res = take(6);
+    // Callers plan with one size rule for both forms: r, u of m, c, v of n,
+    // column partials (one row per 256 rows of xi up to 1024 columns, one per
+    // stripe above), error partials, fold partials of 4 columns each, vector
+    // statistics, results.  Whether a tensor fits the static workspace does
+    // not depend on the form.
+    const int64_t nparts = n <= 1024 ? (m + 255) / 256 : s.nstripes;
+    s.words = m + n + m + n + nparts * n + 2 * s.nerr + 4 * ((n + 3) / 4) + 2 * s.nstat + 6;
+    if (end > s.words) s.words = end;
     return s;
 }
 
@@ -770,7 +796,9 @@ rikfad_status report_on(const float *xi, int64_t m, int64_t n, double eps_stab,
                         int32_t power_iters, hipStream_t st, const ReportShape &sh, double *buf,
                         rikfad_friction_stats *out)
 {
-    double *stats_r;                        // results: R (2), u (2), errors (2)
+    double *c = buf + sh.c, *v = buf + sh.v, *cpart = buf + sh.cpart;
+    double *cfold = buf + sh.cfold, *vfold = buf + sh.vfold, *epart = buf + sh.epart;
+    double *stats_r = buf + sh.res;         // results: R (2), u (2), errors (2)
     const int nfold = static_cast<int>(sh.nfold);
     const dim3 fold_grid(static_cast<uint32_t>(nfold));
     if (sh.nblk) {
@@ -778,10 +806,7 @@ rikfad_status report_on(const float *xi, int64_t m, int64_t n, double eps_stab,
         // first power iteration (from v = C) also sums |xi|_F^2 and
         // |xi - xi~|_F^2; the last pass forms |xi v| for the final unit
         // vector v.
-        double *c = buf, *v = c + sh.stride, *cpart = v + sh.stride;
-        double *cfold = cpart + sh.nblk * sh.stride, *vfold = cfold + 2 * sh.nfold;
-        double *epart = vfold + 2 * sh.nfold, *upart = epart + 2 * sh.nblk;
-        stats_r = upart + 2 * sh.nblk;
+        double *upart = buf + sh.spart;
         OnePass a{xi, m, n, sh.rows, nfold, nullptr, nullptr, eps_stab, cpart, epart, sh.stride};
         auto fold = [&](double *out, double *parts) {
             hipLaunchKernelGGL(col_fold_kernel, fold_grid, dim3(kT), 0, st, cpart, sh.stride, n,
@@ -806,10 +831,7 @@ rikfad_status report_on(const float *xi, int64_t m, int64_t n, double eps_stab,
     } else {
         const int64_t stripe = sh.stripe, nerr = sh.nerr;
         const int nstripes = static_cast<int>(sh.nstripes);
-        double *r = buf, *c = r + m, *u = c + n, *v = u + m;
-        double *cpart = v + n, *epart = cpart + nstripes * n, *cfold = epart + 2 * nerr;
-        double *vfold = cfold + 2 * sh.nfold, *spart = vfold + 2 * sh.nfold;
-        stats_r = spart + 2 * sh.nstat;
+        double *r = buf + sh.r, *u = buf + sh.u, *spart = buf + sh.spart;
         double *stats_u = stats_r + 2, *err = stats_u + 2;
         const dim3 rows_grid(static_cast<uint32_t>((m + kT / 64 - 1) / (kT / 64)));
         const dim3 cols_grid(static_cast<uint32_t>(sh.ncb), static_cast<uint32_t>(nstripes));
