@@ -262,7 +262,7 @@ void ikfad_destroy(ikfad_ctx *ctx);
  * |xi|_F^2 / sigma_1^2.  All reductions are fp64 in a fixed order.
  * Blocking (waits for `stream`); allocates and frees a temporary device
  * workspace (rikfad_friction_report_workspace_bytes gives its size).  For
- * 4 <= n <= 16384 the report reads xi power_iters + 2 times (C in one pass,
+ * n <= 16384 the report reads xi power_iters + 2 times (C in one pass,
  * the errors with the first power iteration, sigma_1 in a last pass) and
  * keeps at most 256 rows of n column partial sums (8 bytes each, up to the
  * size of the static workspace below); otherwise it reads xi

@@ -16,7 +16,7 @@
 // so the leading singular vectors are non-negative), normalised on the GPU:
 // the column fold also writes per-workgroup squared-norm partials, from
 // which every wave of the next pass derives the same scale.  For
-// 4 <= n <= 16384 every pass reads xi once (u = xi v and xi^T u together).
+// n <= 16384 every pass reads xi once (u = xi v and xi^T u together).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -180,10 +180,11 @@ __device__ __forceinline__ double sum_waves(double v)
 
 // ---------------------------------------------------------- one-pass kernels
 //
-// One pass over xi for 4 <= n <= 16384, reading it once.  WPR of a
-// workgroup's 16 waves cover a row with K 16-byte loads per lane, so 16 / WPR
-// groups of waves work on consecutive shares of the workgroup's rows.  A lane
-// keeps its 4 K columns' weights and column sums in registers; for each row it
+// One pass over xi for n <= 16384, reading it once.  WPR of a workgroup's 16
+// waves cover a row with K 16-byte loads per lane (V = 4; V = 1, one 4-byte
+// load, for rows of fewer than 4 columns), so 16 / WPR groups of waves work on
+// consecutive shares of the workgroup's rows.  A lane keeps its V K columns'
+// weights and column sums in registers; for each row it
 // forms its share of the weighted sum s_i = sum_j xi[i, j] w_j, the sum is
 // completed in the wave (across WPR waves through LDS), and xi[i, j] s_i is
 // added to the column sums, rows in order.  The next row's loads go out
@@ -213,6 +214,9 @@ enum : int { kPassSums = 0, kPassPower = 1, kPassPowerErr = 2, kPassNorm = 3 };
 
 // Rows of xi start at any 4-byte boundary when n is not a multiple of 4.
 typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x1 __attribute__((ext_vector_type(1)));
+template <int V> struct RowAccess { typedef f32x4a4 type; };
+template <> struct RowAccess<1> { typedef f32x1 type; };
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
@@ -229,14 +233,15 @@ struct OnePass {
 
 constexpr int kPassWaves = 16;
 
-template <int K, int WPR, int MODE>
+template <int K, int WPR, int MODE, int V = 4>
 __global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
 {
+    static_assert(V == 4 || (V == 1 && K == 1 && WPR == 1), "one column per lane: one wave per row");
     constexpr bool kWeighted = MODE != kPassSums;
     constexpr bool kErr = MODE == kPassPowerErr;
     constexpr bool kCols = MODE != kPassNorm;
     constexpr int NW = kPassWaves, LT = 64 * WPR, NG = NW / WPR;
-    __shared__ double lds[NG > 1 ? NG * 4 * K * LT : 1];
+    __shared__ double lds[NG > 1 ? NG * V * K * LT : 1];
     __shared__ double rowsum[2][WPR > 1 ? NG : 1][WPR], rowsum1[2][WPR > 1 ? NG : 1][WPR];
     __shared__ double ls[NW][2];
     const int lane = threadIdx.x & 63;
@@ -248,16 +253,16 @@ __global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
     const int lt = sub * 64 + lane;
     const int n = static_cast<int>(a.n);
 
-    // Columns 4 (lt + k LT) .. + 3.  Only the last load can pass the row's
-    // end: it then reads the row's last four elements and masks the ones
-    // that another lane owns (all four where none is left).
+    // Columns V (lt + k LT) .. + V - 1.  Only the last load can pass the row's
+    // end: it then reads the row's last V elements and masks the ones
+    // that another lane owns (all of them where none is left).
     int lc[K];
-    uint32_t keep[4];
+    uint32_t keep[V];
 #pragma unroll
-    for (int k = 0; k < K; ++k) lc[k] = min(4 * (lt + k * LT), n - 4);
-    const int skip = min(4 * (lt + (K - 1) * LT) - lc[K - 1], 4);
+    for (int k = 0; k < K; ++k) lc[k] = min(V * (lt + k * LT), n - V);
+    const int skip = min(V * (lt + (K - 1) * LT) - lc[K - 1], V);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) keep[i] = i >= skip ? 0xffffffffu : 0u;
+    for (int i = 0; i < V; ++i) keep[i] = i >= skip ? 0xffffffffu : 0u;
 
     const int64_t wg0 = static_cast<int64_t>(blockIdx.x) * a.rows;
     const int share = (a.rows + NG - 1) / NG;
@@ -267,22 +272,23 @@ __global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
     const int64_t rlast = nr > 0 ? rend - 1 : a.m - 1;  // a row of xi
 
     // Row q of the group's share; past its last, the last again.
-    auto load = [&](int q, f32x4a4 (&x)[K]) {
+    typedef typename RowAccess<V>::type access;
+    auto load = [&](int q, access (&x)[K]) {
         const DG float *xr = gp(a.xi) + min(r0 + q, rlast) * a.n;
 #pragma unroll
-        for (int k = 0; k < K; ++k) x[k] = *reinterpret_cast<const DG f32x4a4 *>(xr + lc[k]);
+        for (int k = 0; k < K; ++k) x[k] = *reinterpret_cast<const DG access *>(xr + lc[k]);
     };
 
     // The first row goes out ahead of the weights' loads, so that the two
     // chains overlap.
-    f32x4a4 nx[K];
+    access nx[K];
     load(0, nx);
 
-    double w[K][4], acc[K][4];
+    double w[K][V], acc[K][V];
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < V; ++i) {
             w[k][i] = kWeighted ? gp(a.v)[lc[k] + i] : 1.0;
             acc[k][i] = 0.0;
         }
@@ -291,7 +297,7 @@ __global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
 #pragma unroll
         for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[k][i] *= scale;
+            for (int i = 0; i < V; ++i) w[k][i] *= scale;
     }
     double inv = 0.0;
     if (kErr) {
@@ -301,12 +307,12 @@ __global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
 
     double sa = 0.0, sb = 0.0;
     for (int q = 0; q < share; ++q) {           // the same count in every group
-        float x[K][4];
+        float x[K][V];
         const uint32_t ok = q < nr ? 0xffffffffu : 0u;
 #pragma unroll
         for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < V; ++i)
                 x[k][i] = __uint_as_float(__float_as_uint(nx[k][i]) &
                                           (k == K - 1 ? ok & keep[i] : ok));
         load(q + 1, nx);
@@ -315,7 +321,7 @@ __global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
 #pragma unroll
             for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < V; ++i) {
                     s += static_cast<double>(x[k][i]) * w[k][i];
                     if (kErr) s1 += static_cast<double>(x[k][i]);
                 }
@@ -337,7 +343,7 @@ __global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
 #pragma unroll
         for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < V; ++i) {
                 const double xv = x[k][i];
                 if (kCols) acc[k][i] += kWeighted ? xv * s : xv;
                 if (kErr) {
@@ -356,17 +362,17 @@ __global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
 #pragma unroll
             for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) lds[(grp * K + k) * 4 * LT + 4 * lt + i] = acc[k][i];
+                for (int i = 0; i < V; ++i) lds[(grp * K + k) * V * LT + V * lt + i] = acc[k][i];
             __syncthreads();
-            for (int j = threadIdx.x; j < 4 * K * LT; j += 64 * NW) {
+            for (int j = threadIdx.x; j < V * K * LT; j += 64 * NW) {
                 double t = lds[j];
 #pragma unroll
-                for (int g = 1; g < NG; ++g) t += lds[g * K * 4 * LT + j];
+                for (int g = 1; g < NG; ++g) t += lds[g * K * V * LT + j];
                 // slot j is element i of the lane whose first column is j - i
-                const int i = j & 3, c0 = j - i, d = min(c0 - min(c0, n - 4), 4);
+                const int i = j & (V - 1), c0 = j - i, d = min(c0 - min(c0, n - V), V);
                 if (i >= d) gp(out)[c0 - d + i] = t;
             }
-        } else {
+        } else if constexpr (V == 4) {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if (k < K - 1 || skip == 0) {       // whole groups of 4: 32-byte aligned
@@ -375,7 +381,7 @@ __global__ __launch_bounds__(64 * kPassWaves) void onepass_kernel(OnePass a)
                     q[1] = f64x2{acc[k][2], acc[k][3]};
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < V; ++i)
                         if (keep[i] != 0u) gp(out)[lc[k] + i] = acc[k][i];
                 }
             }
@@ -705,7 +711,7 @@ ReportShape report_shape(int64_t m, int64_t n)
     };
     s.stride = (n + 3) / 4 * 4;
     s.nblk = s.rows = 0;
-    if (n >= 4 && n <= kOnePassMaxCols) {
+    if (n <= kOnePassMaxCols) {
         // The rest of the static workspace bounds the partial sums (only
         // above 8000 columns: 187 workgroups for 4096 x 11008).
         const int64_t fixed = 2 * s.stride + 4 * s.nfold + 6 + 16;
@@ -778,7 +784,8 @@ void launch_onepass(const OnePass &a, int nblk, hipStream_t st)
         hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>(nblk)), dim3(64 * kPassWaves), 0, st,
                            a);
     };
-    if (a.n <= 256) go(onepass_kernel<1, 1, MODE>);
+    if (a.n < 4) go(onepass_kernel<1, 1, MODE, 1>);
+    else if (a.n <= 256) go(onepass_kernel<1, 1, MODE>);
     else if (a.n <= 512) go(onepass_kernel<2, 1, MODE>);
     else if (a.n <= 768) go(onepass_kernel<3, 1, MODE>);
     else if (a.n <= 1024) go(onepass_kernel<4, 1, MODE>);

@@ -16,12 +16,12 @@ from parity import log
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
 
-# Widths below 4 and above 16384 take the two-pass iteration, the tall ones
-# with many stripes of column partial sums.
-SHAPES = [(9, 3), (1000, 3), (5000, 2), (33000, 1), (40000, 3), (40, 4), (33, 5), (300, 255),
+# Widths below 4 take one column per lane (workgroups of 16 rows and of
+# more), widths above 16384 the two-pass iteration.
+SHAPES = [(9, 3), (1000, 3), (5000, 2), (33000, 1), (40000, 3), (1, 1), (40, 4), (33, 5), (300, 255),
           (17, 256), (16, 257), (5000, 513), (15, 769), (4099, 1023), (1, 1024), (3, 2047),
           (9, 2049), (1030, 4096), (5, 4097), (21, 8193), (6, 12289), (13, 16383), (7, 16384),
-          (3, 16385)]
+          (3, 16385), (2049, 16390)]
 
 
 @pytest.mark.parametrize("m,n", SHAPES, ids=[f"{m}x{n}" for m, n in SHAPES])

@@ -25,20 +25,26 @@ def _planned_words(m, n):
             + 2 * -(-max(m, n) // 4096) + 6)
 
 
-def _two_pass_words(m, n):
-    """What the two-pass form (n < 4 and n > 16384) writes: one row of column
-    partial sums per stripe, one pair per 16 rows of errors, per 16 columns
-    of either fold and per 4096 elements of the vector statistics."""
-    return (2 * (m + n) + _stripes(m, n) * n + 2 * -(-m // 16) + 4 * -(-n // 16)
-            + 2 * -(-max(m, n) // 4096) + 6)
+def _laid_out_words(m, n):
+    """What the form that runs writes.  One pass over xi (n <= 16384): C and v
+    padded to whole groups of 4, a row of column partial sums and a pair of
+    errors and of norms per workgroup (at least 16 rows each up to 1024
+    columns, at most 256 of them), a pair per 16 columns of either fold, the
+    results.  Two passes: one row of column partial sums per stripe, a pair
+    per 16 rows of errors and per 4096 elements of the vector statistics."""
+    fold = 4 * -(-n // 16) + 6
+    if n <= 1024:
+        nblk = -(-m // max(16, -(-m // 256)))
+        return 2 * (-n % 4 + n) + nblk * (-n % 4 + n + 4) + fold
+    return 2 * (m + n) + _stripes(m, n) * n + 2 * -(-m // 16) + fold + 2 * -(-max(m, n) // 4096)
 
 
-@pytest.mark.parametrize("n", [1, 2, 3, 16385, 50257])
-def test_workspace_holds_what_the_two_pass_form_writes(n):
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 255, 1024, 16385, 50257])
+def test_workspace_holds_what_its_form_writes(n):
     for m in [1, 2, 15, 16, 17, 31, 33, 255, 256, 257, 1000, 1025, 4099, 5000, 32767, 32769, 50257,
               70000, 131073, 200000, 524287, 524289, 980000, 2000003]:
         got = R.rikfad_friction_report_workspace_bytes(m, n)
-        assert got >= 8 * _two_pass_words(m, n), (m, n, got)
+        assert got >= 8 * _laid_out_words(m, n), (m, n, got)
 
 
 def test_noalloc_accepts_what_fits_the_planned_size():
