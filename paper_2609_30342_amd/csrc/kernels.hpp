@@ -19,10 +19,12 @@ hipError_t launch_stream(const TensorDesc *tensors, const void *const *grads, co
                          hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 
 // Finalisation of R, C and the partial sums of R (init_only: sums only),
-// in workgroups of 2^fin_log2 threads (the plan's choice).
-hipError_t launch_finalize(const FinItem *items, int64_t nitems, int fin_log2, float *ws,
-                           const Coeffs &k, int *flag, int init_only, hipStream_t stream,
-                           hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
+// in workgroups of 2^fin_log2 threads (the plan's choice); wide: some items
+// are FIN_ROWS_WIDE.
+hipError_t launch_finalize(const FinItem *items, int64_t nitems, int fin_log2, bool wide,
+                           float *ws, const Coeffs &k, int *flag, int init_only,
+                           hipStream_t stream, hipEvent_t start = nullptr,
+                           hipEvent_t stop = nullptr);
 
 // Second half-kick + D over the matrix tiles of every tile group.
 hipError_t launch_apply(const TensorDesc *tensors, const Tile *tiles, const TileGroup *groups,

@@ -355,6 +355,7 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
         // one workgroup), so such matrices get one item per 256 rows whose
         // waves share the blocks.
         const bool split = wide && d.ncb > kFinWideBlocks;
+        pl.fin_wide = pl.fin_wide || split;
         const int64_t rows = split ? kChunkRows : 4 * fin_threads;
         for (int64_t r0 = 0; r0 < d.m; r0 += rows)
             pl.fin.push_back({d.r, d.m, d.rowpart, d.chunk + r0 / kChunkRows,

@@ -20,6 +20,7 @@ struct Plan {
     std::vector<FinItem> fin;         // row items, then column items
     int64_t row_items = 0;
     int32_t fin_log2 = kFinSmallLog2; // log2 of the finalisation workgroup size
+    bool fin_wide = false;            // some row items are FIN_ROWS_WIDE
     int64_t ws_floats = 0;            // partial-sum workspace (floats)
     int64_t matrices = 0, vectors = 0, elements = 0;
     int64_t state_bytes = 0, ikfad_state_bytes = 0, min_bytes = 0, stream_min_bytes = 0;

@@ -102,6 +102,7 @@ static void check_wide_plan(const Plan &pl, int64_t count)
         else check_matrix_tile(pl, tl, elems, rowp, colp);
     }
     const int T = 1 << pl.fin_log2, W = T / kWave;
+    bool wide = false;
     for (size_t q = 0; q < pl.fin.size(); ++q) {
         const FinItem &it = pl.fin[q];
         const size_t ti = static_cast<size_t>(it.tensor);
@@ -112,6 +113,7 @@ static void check_wide_plan(const Plan &pl, int64_t count)
             continue;
         }
         CHECK(it.kind == (td.ncb > kFinWideBlocks ? FIN_ROWS_WIDE : FIN_ROWS), "row item kind");
+        wide = wide || it.kind == FIN_ROWS_WIDE;
         for (int j = 0; j < it.count; ++j) rows[ti].hit(int64_t(it.start) + j, "row item");
         CHECK(it.f == td.r && it.len == td.m && it.part == td.rowpart && it.nparts == td.ncb,
               "row item descriptor");
@@ -144,6 +146,7 @@ static void check_wide_plan(const Plan &pl, int64_t count)
             CHECK(seen[static_cast<size_t>(b)] == 1, "block %d read %d times", b,
                   seen[static_cast<size_t>(b)]);
     }
+    CHECK(pl.fin_wide == wide, "finalisation form");
     for (size_t i = 0; i < nt; ++i) {
         const TensorDesc &td = pl.tensors[i];
         CHECK(elems[i].all(), "tensor %lldx%lld not covered", (long long)td.m, (long long)td.n);
