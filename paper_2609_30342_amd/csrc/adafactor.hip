@@ -51,7 +51,11 @@ struct Lanes {
     int lane, llog, L, G, seg, nr, nld;
     bool colok;
     int skip;          // ragged rows: the lane owns elements skip .. V - 1 of its access
-    int64_t lcol, r0;
+    // lcol: column of the lane's access; col: the same outside ragged rows, and
+    // used there, because the update kernel then takes 68 registers in fp32
+    // instead of 64: three workgroups of a compute unit stream faster than four
+    // (8 x 4096 x 4096: 429 us, 436 with four).
+    int64_t col, lcol, r0;
     int64_t r_any;     // a row of the tile this wave may read: r0, or the tile's first row
 };
 
@@ -66,7 +70,8 @@ __device__ __forceinline__ Lanes lanes_of(const Tile &tile, int64_t n)
     t.seg = t.lane >> t.llog;
     const int ccol = (t.lane & (t.L - 1)) * V;
     t.colok = ccol < tile.ncols;
-    t.lcol = t.colok ? tile.col0 + ccol : tile.col0;   // lanes past the block read its first
+    t.col = tile.col0 + ccol;
+    t.lcol = t.colok ? t.col : tile.col0;   // lanes past the block read its first column
     t.skip = 0;
     if (RAG) {                              // see the R-iKFAD streaming pass
         const int64_t c = t.lcol;
@@ -189,12 +194,13 @@ __device__ __forceinline__ float row_factor(float r, float inv_s)
 __device__ __forceinline__ float col_factor(float c) { return c > 0.f ? rsqrtf(c) : 0.f; }
 
 // Per-row factors of a matrix tile: lane t holds row r0 + t's, columns in fc.
-template <int V>
+template <int V, bool RAG>
 __device__ __forceinline__ float tile_factors(const TensorDesc &td, const Lanes &t,
                                               const float *__restrict__ ws, float (&fc)[V])
 {
 #pragma unroll
-    for (int i = 0; i < V; ++i) fc[i] = t.colok ? col_factor(gmem(td.c)[t.lcol + i]) : 0.f;
+    for (int i = 0; i < V; ++i)
+        fc[i] = t.colok ? col_factor(gmem(td.c)[(RAG ? t.lcol : t.col) + i]) : 0.f;
     const float s = sum_r(ws + td.chunk, td.nchunk);
     const float inv_s = s > 0.f ? 1.f / s : 0.f;
     return t.lane < t.nr ? row_factor(gmem(td.r)[t.r0 + t.lane], inv_s) : 0.f;
@@ -550,7 +556,7 @@ __device__ void update_matrix(const TensorDesc &td, const XT *__restrict__ g, co
     typename Raw<XT, V>::type gr[B], xr[B];
     float mv[B][V];
     float fc[V];
-    const float myfr = FOLD ? read_factors<V>(td, t, ws, fc) : tile_factors<V>(td, t, ws, fc);
+    const float myfr = FOLD ? read_factors<V>(td, t, ws, fc) : tile_factors<V, RAG>(td, t, ws, fc);
     if (t.nld > 0) {
 #pragma unroll
         for (int u = 0; u < B; ++u) {
@@ -576,7 +582,7 @@ __device__ void update_matrix(const TensorDesc &td, const XT *__restrict__ g, co
                 xv[i] = xv[i] - mv[u][i];
             }
             if (t.colok && rl < t.nr) {
-                const int64_t off = (t.r0 + rl) * n + t.lcol;
+                const int64_t off = (t.r0 + rl) * n + (RAG ? t.lcol : t.col);
                 if constexpr (RAG) {
                     store_owned<XT>(x + off, xv, t.skip);
                     store_owned<float>(mom + off, mv[u], t.skip);
