@@ -629,15 +629,21 @@ struct UpdateVec {
     }
 };
 
-// scales: one per tensor, or with FOLD the tile sums to fold.
+// scales: one per tensor, or with FOLD the tile sums to fold.  reverse: the RMS
+// pass left the gradients of its last tiles in the memory-side cache, so the
+// tiles are walked from the last to the first, in eights kept in order: a
+// tile stays on the XCD (launch index mod 8) whose L2 the other passes of a
+// small set used (plain reverse order: 2,000 matrices of 16 x 16 8.2 us a pass,
+// 6.9 in launch order).
 template <typename XT, int V, bool RAG, bool FOLD>
 __global__ __launch_bounds__(kStreamThreads) void adafm_update_kernel(
     const TensorDesc *__restrict__ tensors, const void *const *__restrict__ grads,
     const Tile *__restrict__ tiles, int64_t tile0, const float *__restrict__ ws,
-    const float *__restrict__ scales, const TensorRange *__restrict__ ranges, AdaCoeffs k)
+    const float *__restrict__ scales, const TensorRange *__restrict__ ranges, int reverse,
+    AdaCoeffs k)
 {
-    // From the last tile to the first: the RMS pass read those last.
-    const Tile tile = tiles[tile0 + gridDim.x - 1 - blockIdx.x];
+    const uint32_t b = blockIdx.x, whole = reverse & ~7u;    // tiles in whole eights
+    const Tile tile = tiles[tile0 + (b < whole ? whole - 8 - (b & ~7u) + (b & 7u) : b)];
     const TensorDesc td = tensors[tile.tensor];
     const XT *g = static_cast<const XT *>(grads[tile.tensor]);
     const float s = FOLD ? fold_scale(ranges[tile.tensor], scales, k) : gmem(scales)[tile.tensor];
@@ -672,7 +678,7 @@ typedef void (*StatsFn)(const TensorDesc *, const void *const *, const Tile *, i
 typedef void (*RmsFn)(const TensorDesc *, const void *const *, const Tile *, int64_t,
                       const float *, float *, int64_t);
 typedef void (*UpdateFn)(const TensorDesc *, const void *const *, const Tile *, int64_t,
-                         const float *, const float *, const TensorRange *, AdaCoeffs);
+                         const float *, const float *, const TensorRange *, int, AdaCoeffs);
 
 template <bool X2> struct PickStats {
     template <typename XT, int V, bool RAG> StatsFn get() const
@@ -745,24 +751,22 @@ hipError_t launch_adafm_scale(const TensorRange *ranges, int64_t ntensors, const
 hipError_t launch_adafm_update(const TensorDesc *tensors, const void *const *grads,
                                const Tile *tiles, const TileGroup *groups, int ngroups,
                                const float *ws, const float *scales, const TensorRange *ranges,
-                               const AdaCoeffs &k, hipStream_t stream, hipEvent_t start,
-                               hipEvent_t stop)
+                               bool reverse, const AdaCoeffs &k, hipStream_t stream,
+                               hipEvent_t start, hipEvent_t stop)
 {
-    // Groups, too, from the last to the first: `stop` goes on the first one
-    // with tiles.
-    int first = -1;
-    for (int q = ngroups - 1; q >= 0; --q)
-        if (groups[q].count > 0) first = q;
-    for (int q = ngroups - 1; q >= 0; --q) {
-        const TileGroup &gr = groups[q];
+    int left = 0;                       // groups with tiles still to launch
+    for (int q = 0; q < ngroups; ++q) left += groups[q].count > 0;
+    for (int i = 0; i < ngroups; ++i) {
+        const TileGroup &gr = groups[reverse ? ngroups - 1 - i : i];
         if (gr.count <= 0) continue;
         const UpdateFn fn = ranges ? pick<UpdateFn>(gr, PickUpdate<true>())
                                    : pick<UpdateFn>(gr, PickUpdate<false>());
-        hipEvent_t a = start, b = q == first ? stop : nullptr;
+        hipEvent_t a = start, b = --left == 0 ? stop : nullptr;
         start = nullptr;
         const hipError_t e = launch(fn, dim3(static_cast<uint32_t>(gr.count)),
                                     dim3(kStreamThreads), stream, a, b, tensors, grads, tiles,
-                                    gr.begin, ws, scales, ranges, k);
+                                    gr.begin, ws, scales, ranges,
+                                    reverse ? static_cast<int>(gr.count) : 0, k);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -20,7 +20,7 @@ hipError_t launch_adafm_stats(const TensorDesc *tensors, const void *const *grad
 
 // Pass 2: tile sums of U^2 for the matrix tiles (after the factor update).
 // Tiles from keep_from on load the gradient without the non-temporal hint,
-// for the update pass, which runs from the last tile to the first.
+// for the update pass, which then runs from the last tile to the first.
 hipError_t launch_adafm_rms(const TensorDesc *tensors, const void *const *grads,
                             const Tile *tiles, const TileGroup *groups, int ngroups,
                             const float *ws, float *tilepart, int64_t keep_from,
@@ -35,10 +35,11 @@ hipError_t launch_adafm_scale(const TensorRange *ranges, int64_t ntensors, const
 // Pass 3: M <- beta1 M + (1 - beta1) scale U, X <- X - M.  With ranges (no
 // tensor of more than kFoldTiles tiles), scales is tilepart and every wave
 // folds its tensor's tile sums; else scales holds launch_adafm_scale's results.
+// reverse: from the last tile to the first, after an RMS pass that kept some.
 hipError_t launch_adafm_update(const TensorDesc *tensors, const void *const *grads,
                                const Tile *tiles, const TileGroup *groups, int ngroups,
                                const float *ws, const float *scales, const TensorRange *ranges,
-                               const AdaCoeffs &k, hipStream_t stream,
+                               bool reverse, const AdaCoeffs &k, hipStream_t stream,
                                hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 
 }  // namespace rk

@@ -797,7 +797,8 @@ rikfad_status adafm_step(adafm_ctx *ctx, void *stream_)
         if (e != hipSuccess) return hip_fail(e, "launch finalize kernel");
     }
     // RMS pass (when clipping and there are matrices), then the scale kernel.
-    if (ctx->hp.clip_threshold > 0 && pl.matrix_tiles > 0) {
+    const bool rms = ctx->hp.clip_threshold > 0 && pl.matrix_tiles > 0;
+    if (rms) {
         if ((s = tm.phase(2, &t0, &t1)) != RIKFAD_OK) return s;
         e = rk::launch_adafm_rms(ctx->dev.tensors, ctx->dev.grads, ctx->dev.tiles,
                                  pl.groups.data(), ng, ctx->dev.ws, ctx->tilepart,
@@ -817,7 +818,7 @@ rikfad_status adafm_step(adafm_ctx *ctx, void *stream_)
     e = rk::launch_adafm_update(ctx->dev.tensors, ctx->dev.grads, ctx->upd_tiles,
                                 ctx->upd_groups.data(), static_cast<int>(ctx->upd_groups.size()),
                                 ctx->dev.ws, fold ? ctx->tilepart : ctx->scales,
-                                fold ? ctx->ranges_dev : nullptr, k, stream, t0, t1);
+                                fold ? ctx->ranges_dev : nullptr, rms, k, stream, t0, t1);
     if (e != hipSuccess) return hip_fail(e, "launch adafm update kernel");
     tm.end_step();
     ctx->steps = t;

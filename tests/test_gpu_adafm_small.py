@@ -44,9 +44,12 @@ def test_folded_scale_has_the_same_bits(shapes, scale):
 @pytest.mark.parametrize("specs", [
     [S("a", 3000, 768), S("b", 1, 768), S("c", 700, 1000, "bf16"), S("d", 90, 27),
      S("e", 40, 3, "bf16"), S("f", 1, 50, "bf16")],
-], ids=["mixed_types"])
-def test_update_in_reverse_over_several_launches(specs):
-    log(f"[case] adafm reverse update {specs}")
-    _, errs = run_adafm_parity(specs, dict(h=1e-2, scale_parameter=True), 4, seed=9,
-                               label="reverse update")
+    [S(f"t{i}", 5, 8) for i in range(7)], [S(f"t{i}", 5, 8) for i in range(8)],
+    [S(f"t{i}", 5, 8) for i in range(17)],       # below, at and past whole eights of tiles
+], ids=["mixed_types", "7_tiles", "8_tiles", "17_tiles"])
+@pytest.mark.parametrize("clip", [1.0, 0.0])     # without clipping in launch order
+def test_update_in_reverse_over_several_launches(specs, clip):
+    log(f"[case] adafm reverse update {specs} clip={clip}")
+    _, errs = run_adafm_parity(specs, dict(h=1e-2, scale_parameter=True, clip_threshold=clip), 4,
+                               seed=9, label="reverse update")
     assert_ok(errs, label="reverse update")
