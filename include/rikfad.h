@@ -371,8 +371,9 @@ rikfad_status adafm_nonfinite(adafm_ctx *ctx, void *stream, int32_t *out);
 /* Kernel timing as for rikfad_timing_*: ms5[5] = statistics pass, factor
  * finalisation, RMS pass (0 when clipping is off or there are no
  * matrices), scale kernel, update pass, summed over the timed steps since
- * the last read.  A set of at most 8192 update tiles folds the scale into the
- * update pass; a timed step of such a set launches it separately. */
+ * the last read.  Small sets (at most 8192 update tiles, above 2048 with at
+ * least 256 elements each, and no tensor of more than 256 statistics tiles)
+ * fold the scale into the update pass; a timed step launches it separately. */
 rikfad_status adafm_timing_enable(adafm_ctx *ctx, int32_t enable);
 rikfad_status adafm_timing_read(adafm_ctx *ctx, double *ms5, int64_t *steps);
 void adafm_destroy(adafm_ctx *ctx);

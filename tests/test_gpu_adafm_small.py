@@ -22,7 +22,8 @@ S = synth.TensorSpec
     [(3, 5), (1, 7), (40, 256), (2048, 256), (2080, 256), (1, 8192 * 3)],
     [(8192, 256), (8190, 255), (1, 2)],                      # 256 tiles of 32 rows
     [(8224, 256), (64, 64)],                                 # 257: beyond the fold
-], ids=["small", "256_tiles", "257_tiles"])
+    [(8, 8)] * 2048, [(8, 8)] * 2049,        # tiles of a few elements: folded up to 2,048
+], ids=["small", "256_tiles", "257_tiles", "2048_small_tiles", "2049_small_tiles"])
 def test_folded_scale_has_the_same_bits(shapes, scale):
     log(f"[case] adafm folded scale {shapes} scale_parameter={scale}")
     got = []
