@@ -93,12 +93,15 @@ rikfad_status make_tables(const rk::Plan &pl, DeviceTables &d)
 // -> 420; with 1000 tensors four launches lost, 28.3 -> 30.0).  Larger ones go
 // through a small ring of pinned host slots so
 // that the asynchronous copy never reads a buffer the host has reused.
+// A push that fails may have written part of the table: whole stays false until
+// one succeeds, and the next step writes its context's pointers again.
 struct GradRing {
     static constexpr int kSlots = 4;
     static constexpr size_t kMaxByValue = 512;
     const void **host[kSlots] = {};
     hipEvent_t done[kSlots] = {};
     bool used[kSlots] = {};
+    bool whole = true;          // the device table is the one last recorded
     int next = 0;
     size_t count = 0;
 
@@ -125,9 +128,11 @@ struct GradRing {
     }
     rikfad_status push(const void **dev, const void *const *src, hipStream_t stream)
     {
+        whole = false;
         if (count <= kMaxByValue) {
             HIP_TRY(rk::launch_set_grads(dev, src, static_cast<int64_t>(count), stream),
                     "launch gradient table kernel");
+            whole = true;
             return RIKFAD_OK;
         }
         const int s = next;
@@ -138,6 +143,7 @@ struct GradRing {
                 "hipMemcpyAsync gradient table");
         HIP_TRY(hipEventRecord(done[s], stream), "hipEventRecord gradient slot");
         used[s] = true;
+        whole = true;
         return RIKFAD_OK;
     }
 };
@@ -349,6 +355,10 @@ rikfad_status rikfad_step(rikfad_ctx *ctx, void *stream_)
     const rk::Plan &pl = ctx->plan;
     if (pl.tiles.empty()) return RIKFAD_OK;
     hipError_t e;
+    rikfad_status s;
+    if (!ctx->ring.whole &&
+        (s = ctx->ring.push(ctx->dev.grads, ctx->grads_host.data(), stream)) != RIKFAD_OK)
+        return s;
     if (!ctx->sums_valid && pl.row_items > 0) {
         e = rk::launch_finalize(ctx->dev.fin, pl.row_items, pl.fin_log2, pl.fin_wide,
                                 ctx->dev.ws, ctx->k, ctx->dev.flag, 1, stream);
@@ -357,7 +367,6 @@ rikfad_status rikfad_step(rikfad_ctx *ctx, void *stream_)
     ctx->sums_valid = true;
     Timing &tm = ctx->timing;
     hipEvent_t t0, t1;
-    rikfad_status s;
     if ((s = tm.phase(0, &t0, &t1)) != RIKFAD_OK) return s;
     e = rk::launch_stream(ctx->dev.tensors, ctx->dev.grads, ctx->dev.tiles, pl.groups.data(),
                           static_cast<int>(pl.groups.size()), ctx->dev.ws, ctx->k,
@@ -786,6 +795,10 @@ rikfad_status adafm_step(adafm_ctx *ctx, void *stream_)
         ctx->steps = t;
         return RIKFAD_OK;
     }
+    rikfad_status s;
+    if (!ctx->ring.whole &&
+        (s = ctx->ring.push(ctx->dev.grads, ctx->grads_host.data(), stream)) != RIKFAD_OK)
+        return s;
     const rk::AdaCoeffs k = adafm_coeffs(ctx->hp, t);
     rk::Coeffs fk{};            // the factor update R <- b R + (1-b) rowsum
     fk.a = k.b;
@@ -793,7 +806,6 @@ rikfad_status adafm_step(adafm_ctx *ctx, void *stream_)
     const int ng = static_cast<int>(pl.groups.size());
     Timing &tm = ctx->timing;
     hipEvent_t t0, t1;
-    rikfad_status s;
     if ((s = tm.phase(0, &t0, &t1)) != RIKFAD_OK) return s;
     hipError_t e = rk::launch_adafm_stats(ctx->dev.tensors, ctx->dev.grads, ctx->dev.tiles,
                                           pl.groups.data(), ng, ctx->dev.ws, ctx->tilepart, k,
