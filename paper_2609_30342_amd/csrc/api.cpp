@@ -296,7 +296,7 @@ rikfad_status rikfad_state_bytes(const rikfad_tensor *tensors, int64_t count,
     if (!rikfad_bytes || !ikfad_bytes) return fail(RIKFAD_EINVAL, "output pointer is NULL");
     rk::Plan pl;
     std::string err;
-    rikfad_status s = rk::plan_rikfad(tensors, count, pl, err, 0, true);
+    rikfad_status s = rk::plan_rikfad(tensors, count, pl, err);
     if (s != RIKFAD_OK) return fail(s, err);
     *rikfad_bytes = pl.state_bytes;
     *ikfad_bytes = pl.ikfad_state_bytes;
@@ -314,7 +314,7 @@ rikfad_status rikfad_create(const rikfad_tensor *tensors, int64_t count,
     if (s != RIKFAD_OK) return fail(s, err);
     rikfad_ctx *ctx = new (std::nothrow) rikfad_ctx();
     if (!ctx) return fail(RIKFAD_ENOMEM, "host allocation failed");
-    s = rk::plan_rikfad(tensors, count, ctx->plan, err, 0, true);
+    s = rk::plan_rikfad(tensors, count, ctx->plan, err);
     if (s != RIKFAD_OK) {
         delete ctx;
         return fail(s, err);
@@ -743,12 +743,12 @@ rikfad_status adafm_create(const rikfad_tensor *tensors, int64_t count, const ad
     adafm_ctx *ctx = new (std::nothrow) adafm_ctx();
     if (!ctx) return fail(RIKFAD_ENOMEM, "host allocation failed");
     std::string err;
-    if ((s = rk::plan_rikfad(tensors, count, ctx->plan, err, kReadRowsPerWave, true)) != RIKFAD_OK) {
+    if ((s = rk::plan_rikfad(tensors, count, ctx->plan, err, kReadRowsPerWave)) != RIKFAD_OK) {
         delete ctx;
         return fail(s, err);
     }
     if (ctx->plan.matrix_tiles < kReadMinTiles &&
-        (s = rk::plan_rikfad(tensors, count, ctx->plan, err, 0, true)) != RIKFAD_OK) {
+        (s = rk::plan_rikfad(tensors, count, ctx->plan, err)) != RIKFAD_OK) {
         delete ctx;
         return fail(s, err);
     }
@@ -756,7 +756,7 @@ rikfad_status adafm_create(const rikfad_tensor *tensors, int64_t count, const ad
     ctx->grads_host = ctx->plan.grads;
     const size_t ntile = ctx->plan.tiles.size(), nt = ctx->plan.tensors.size();
     rk::Plan upd;
-    if ((s = rk::plan_rikfad(tensors, count, upd, err, kUpdateRowsPerWave, true)) != RIKFAD_OK) {
+    if ((s = rk::plan_rikfad(tensors, count, upd, err, kUpdateRowsPerWave)) != RIKFAD_OK) {
         delete ctx;
         return fail(s, err);
     }

@@ -18,8 +18,9 @@ constexpr int64_t kMaxElems = (int64_t(1) << 62) - 1;
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
-// 128-bit path when rows stay 16-byte aligned, else narrower accesses.
-// bf16 matrices take 4 elements per lane (64-bit x and g accesses).
+// Elements per aligned access of every row: 4 where rows stay 16-byte aligned
+// (bf16 x and g: 8-byte), else 1.  Matrices of 1 here take 4-wide accesses at
+// element alignment if they have the columns (ragged tiles).
 int32_t matrix_vec(const rikfad_tensor &t)
 {
     if (t.dtype == RIKFAD_FP32)
@@ -170,11 +171,11 @@ int matrix_blocks(int64_t n, int32_t vec, bool ragged, int base, std::vector<Blo
 }  // namespace
 
 rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::string &err,
-                          int rows_per_wave, bool wide)
+                          int rows_per_wave)
 {
     // Rows of at least one access; shorter ones stay on the one-column path.
-    auto is_ragged = [wide](const rikfad_tensor &T) {
-        return wide && T.n >= kRaggedVec && matrix_vec(T) == 1;
+    auto is_ragged = [](const rikfad_tensor &T) {
+        return T.n >= kRaggedVec && matrix_vec(T) == 1;
     };
     if (count < 0 || (count > 0 && !t)) {
         err = "tensor list is NULL or count < 0";
@@ -354,7 +355,7 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
         // loads sets the launch's time (768 x 50257: 197 blocks, 50 rounds,
         // one workgroup), so such matrices get one item per 256 rows whose
         // waves share the blocks.
-        const bool split = wide && d.ncb > kFinWideBlocks;
+        const bool split = d.ncb > kFinWideBlocks;
         pl.fin_wide = pl.fin_wide || split;
         const int64_t rows = split ? kChunkRows : 4 * fin_threads;
         for (int64_t r0 = 0; r0 < d.m; r0 += rows)

@@ -31,13 +31,12 @@ struct Plan {
 // rows_per_wave > 0 fixes the rows per wave of every matrix tile (narrow
 // blocks still scale it up); 0 takes kRowsPerWave, halved for sets with
 // fewer matrix tiles than the chip has compute units.
-// wide: rows whose length or alignment breaks 16-byte accesses (8-byte bf16
-// ones) get 4-wide tiles at element alignment instead of one-column tiles
-// where they have at least 4 columns, and the row items of matrices with many
-// column blocks are split over more workgroups (FIN_ROWS_WIDE).  The library
-// plans every context this way.
+// Rows whose length or alignment breaks 16-byte accesses (8-byte bf16 ones)
+// get 4-wide tiles at element alignment, one-column tiles where they have
+// fewer than 4 columns; the row items of matrices with many column blocks are
+// split over more workgroups (FIN_ROWS_WIDE).
 rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &out, std::string &err,
-                          int rows_per_wave = 0, bool wide = false);
+                          int rows_per_wave = 0);
 
 // Validates and plans a full-tensor iKFAD context (every tensor element-wise).
 rikfad_status plan_ikfad(const ikfad_tensor *t, int64_t count, Plan &out, std::string &err);

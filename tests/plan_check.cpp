@@ -113,6 +113,63 @@ static void check_matrix_tile(const Plan &pl, const Tile &tl, std::vector<Marks>
                                                  "colpart");
 }
 
+// The same for ragged tiles: 4-wide accesses at element alignment, the last
+// lane of a row masking the elements it does not own.
+static void check_ragged_tile(const Plan &pl, const Tile &tl, std::vector<Marks> &elems,
+                              std::vector<Marks> &rowp, std::vector<Marks> &colp)
+{
+    const TensorDesc &td = pl.tensors[static_cast<size_t>(tl.tensor)];
+    const int64_t m = td.m, n = td.n, mn = m * n;
+    const int V = tl.vec, llog = tl.lanes_log2, L = 1 << llog, G = kWave >> llog;
+    const size_t ti = static_cast<size_t>(tl.tensor);
+    CHECK(V == kRaggedVec && n >= V && td.vec == 1, "ragged tile of %lld columns, vec %d",
+          (long long)n, td.vec);
+    CHECK(tl.rpw >= 1 && tl.rpw <= kMaxRowsPerWave, "rpw %d", tl.rpw);
+    CHECK(tl.ncols >= 1 && tl.ncols <= L * V && tl.col0 % V == 0, "ncols %d", tl.ncols);
+    CHECK(tl.col0 + tl.ncols == n || tl.ncols % V == 0, "partial lane inside a row");
+    CHECK(tl.count <= kStreamWaves * tl.rpw && tl.start + tl.count <= m, "row range");
+    std::vector<int> lds(static_cast<size_t>(tl.ncols), 0);
+    for (int wave = 0; wave < kStreamWaves; ++wave) {
+        const int64_t r0 = tl.start + int64_t(wave) * tl.rpw;
+        int nr = static_cast<int>(tl.start + tl.count - r0);
+        nr = nr < 0 ? 0 : (nr > tl.rpw ? tl.rpw : nr);
+        const int nld = (nr + G - 1) >> (6 - llog);
+        for (int lane = 0; lane < kWave; ++lane) {
+            const int seg = lane >> llog, ccol = (lane & (L - 1)) * V;
+            const bool colok = ccol < tl.ncols;
+            const int64_t c = colok ? tl.col0 + ccol : tl.col0;
+            const int64_t lcol = c < n - V ? c : n - V;
+            const int skip = static_cast<int>(c - lcol);
+            CHECK(lcol >= 0 && lcol + V <= n && skip >= 0 && skip < V, "column %lld skip %d",
+                  (long long)lcol, skip);
+            // rows of a load: the wave's own, else its first; the read passes
+            // of a wave without rows use the tile's first
+            for (int rl = 0; rl < kMaxRowsPerWave + G; ++rl) {
+                const int64_t row = rl < nr ? r0 + rl : nr > 0 ? r0 : tl.start;
+                CHECK(row * n + lcol + V <= mn, "load past the tensor");
+            }
+            for (int ld = 0; ld < nld; ++ld) {
+                const int rl = ld * G + seg;
+                if (!colok || rl >= nr) continue;
+                for (int i = skip; i < V; ++i)
+                    elems[ti].hit((r0 + rl) * n + lcol + i, "element");
+            }
+            if (wave == 0 && lane < L && colok)
+                for (int i = skip; i < V; ++i) {
+                    const int j = ccol - skip + i;
+                    CHECK(j >= 0 && j < tl.ncols, "column slot %d of %d", j, tl.ncols);
+                    if (j >= 0 && j < tl.ncols) lds[static_cast<size_t>(j)] += 1;
+                }
+            if (lane < nr) rowp[ti].hit(int64_t(tl.cb) * pad4(m) + r0 + lane, "rowpart");
+        }
+    }
+    for (int j = 0; j < tl.ncols; ++j) {
+        CHECK(lds[static_cast<size_t>(j)] == 1, "column slot %d written %d times", j,
+              lds[static_cast<size_t>(j)]);
+        colp[ti].hit(colpart_index(tl.col0 + j, tl.stripe, td.nrs), "colpart");
+    }
+}
+
 static void check_vector_tile(const Plan &pl, const Tile &tl, std::vector<Marks> &elems)
 {
     const TensorDesc &td = pl.tensors[static_cast<size_t>(tl.tensor)];
@@ -161,7 +218,8 @@ static void check_plan(const Plan &pl, int64_t count)
     }
     // groups partition the tile table, one group per storage type; a
     // group's matrix tiles are its own width or one-column (served by the
-    // same instantiation), and a one-column group holds no wider tile.
+    // same instantiation), and a one-column group holds no wider tile; a
+    // group is ragged exactly when it holds a ragged tile.
     int64_t covered = 0;
     int ngroups[2] = {0, 0};
     for (const TileGroup &g : pl.groups) {
@@ -172,26 +230,71 @@ static void check_plan(const Plan &pl, int64_t count)
         CHECK(ngroups[dt] == 0, "two groups of one storage type");
         ++ngroups[dt];
         covered += g.count;
+        bool any_ragged = false;
         for (int64_t t = g.begin; t < g.begin + g.count; ++t) {
             const Tile &tl = pl.tiles[static_cast<size_t>(t)];
             CHECK(tl.dtype == g.dtype, "tile dtype vs group");
-            if (tl.kind == KIND_MATRIX) CHECK(tl.vec == g.vec || tl.vec == 1, "tile vec vs group");
+            if (tl.kind != KIND_MATRIX) continue;
+            CHECK(tl.vec == g.vec || tl.vec == 1, "tile vec vs group");
+            const TensorDesc &td = pl.tensors[static_cast<size_t>(tl.tensor)];
+            CHECK((tl.ragged != 0) == (td.vec == 1 && td.n >= kRaggedVec), "tile form of %lld columns",
+                  (long long)td.n);
+            any_ragged = any_ragged || tl.ragged;
         }
+        CHECK((g.ragged != 0) == any_ragged && (!g.ragged || g.vec == kRaggedVec), "ragged group");
     }
     CHECK(covered == static_cast<int64_t>(pl.tiles.size()), "groups do not cover tiles");
     for (const Tile &tl : pl.tiles) {
-        if (tl.kind == KIND_MATRIX) check_matrix_tile(pl, tl, elems, rowp, colp);
-        else check_vector_tile(pl, tl, elems);
+        if (tl.kind != KIND_MATRIX) check_vector_tile(pl, tl, elems);
+        else if (tl.ragged) check_ragged_tile(pl, tl, elems, rowp, colp);
+        else check_matrix_tile(pl, tl, elems, rowp, colp);
     }
     // finalisation items: replays rikfad_finalize_kernel's indexing (4 rows
     // or 4 columns per thread, 16-byte partial-sum reads)
-    const int T = 1 << pl.fin_log2;
+    const int T = 1 << pl.fin_log2, W = T / kWave;
+    bool wide = false;
     const int64_t nfin = static_cast<int64_t>(pl.fin.size());
     for (int64_t q = 0; q < nfin; ++q) {
         const FinItem &it = pl.fin[static_cast<size_t>(q)];
         const TensorDesc &td = pl.tensors[static_cast<size_t>(it.tensor)];
         CHECK(td.kind == KIND_MATRIX, "finalisation item on a vector");
-        if (it.kind == FIN_ROWS) {
+        if (it.kind != FIN_COLS)
+            CHECK(it.kind == (td.ncb > kFinWideBlocks ? FIN_ROWS_WIDE : FIN_ROWS), "row item kind");
+        if (it.kind == FIN_ROWS_WIDE) {
+            // every wave: rows 4 lane .. + 3; the waves share the blocks
+            wide = true;
+            CHECK(q < pl.row_items, "row item after the row range");
+            CHECK(it.count >= 1 && it.count <= kChunkRows && it.start % kChunkRows == 0 &&
+                      it.chunk == td.chunk + it.start / kChunkRows, "split row item");
+            CHECK(it.f == td.r && it.len == td.m && it.part == td.rowpart && it.nparts == td.ncb,
+                  "row item descriptor");
+            const int64_t mp = pad4(td.m);
+            const int per = (it.nparts + W - 1) / W, NL = kFinWideLoads(T);
+            std::vector<int> seen(static_cast<size_t>(it.nparts), 0);
+            for (int w = 0; w < W; ++w) {
+                const int b0 = w * per < it.nparts ? w * per : it.nparts;
+                const int b1 = b0 + per < it.nparts ? b0 + per : it.nparts;
+                for (int cb = b0; cb < b1; cb += NL)
+                    for (int u = 0; u < NL; ++u) {
+                        const int blk = cb + u < b1 ? cb + u : b1 - 1;
+                        for (int lane = 0; 4 * lane < it.count; ++lane) {
+                            const int64_t off = int64_t(blk) * mp + it.start + 4 * lane;
+                            CHECK(off % 4 == 0 && off + 4 <= int64_t(td.ncb) * mp, "rowpart read");
+                            for (int j = 0; j < 4 && 4 * lane + j < it.count; ++j)
+                                CHECK(rowp[static_cast<size_t>(it.tensor)]
+                                          .v[static_cast<size_t>(off + j)] == 1,
+                                      "rowpart read before written");
+                        }
+                        if (cb + u < b1) seen[static_cast<size_t>(blk)] += 1;
+                    }
+            }
+            for (int blk = 0; blk < it.nparts; ++blk)
+                CHECK(seen[static_cast<size_t>(blk)] == 1, "block %d read %d times", blk,
+                      seen[static_cast<size_t>(blk)]);
+            for (int j = 0; j < it.count; ++j)
+                rows[static_cast<size_t>(it.tensor)].hit(int64_t(it.start) + j, "row item row");
+            chunks[static_cast<size_t>(it.tensor)].hit(it.chunk - td.chunk, "chunk");
+        } else if (it.kind == FIN_ROWS) {
             CHECK(q < pl.row_items, "row item after the row range");
             CHECK(it.count >= 1 && it.count <= 4 * T, "row item count");
             CHECK(it.start % (4 * T) == 0 && it.chunk == td.chunk + it.start / kChunkRows,
@@ -218,7 +321,7 @@ static void check_plan(const Plan &pl, int64_t count)
                 for (int j = 0; j < nv; ++j)
                     rows[static_cast<size_t>(it.tensor)].hit(i0 + j, "row item row");
             }
-            for (int w = 0; w < T / kWave; ++w)
+            for (int w = 0; w < W; ++w)
                 if (w * kChunkRows < it.count)
                     chunks[static_cast<size_t>(it.tensor)].hit(it.chunk - td.chunk + w, "chunk");
         } else {
@@ -276,6 +379,7 @@ static void check_plan(const Plan &pl, int64_t count)
                           seen[static_cast<size_t>(st) * ncol + c]);
         }
     }
+    CHECK(pl.fin_wide == wide, "finalisation form");
     for (int64_t i = 0; i < count; ++i) {
         const TensorDesc &td = pl.tensors[static_cast<size_t>(i)];
         CHECK(elems[static_cast<size_t>(i)].all(), "tensor %lld (%lldx%lld) not fully covered",

@@ -1,4 +1,4 @@
-"""Index checks of the library's own tables (ragged tiles, split row items)
+"""Index checks of the tables of mostly ragged sets and of split row items
 on the CPU, with address and undefined-behaviour sanitizers."""
 import os
 import subprocess
