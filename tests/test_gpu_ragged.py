@@ -46,6 +46,19 @@ def test_split_row_items(specs):
     assert_ok(errs, label="split rows")
 
 
+@pytest.mark.parametrize("n", [5, 8])
+def test_more_partial_sums_of_r_than_one_round(n):
+    """140,000 rows: 547 partial sums of R, past the 512 that the short launch's
+    form and the read passes load at once."""
+    specs = [S("tall", 140000, n), S("tall16", 140000, n, "bf16")]
+    log(f"[case] 547 partial sums of R, {n} columns")
+    _, errs = run_parity(specs, synth.HP_FRICTION, 3, seed=13, label="tall")
+    assert_ok(errs, label="tall")
+    _, errs = run_adafm_parity(specs, dict(h=1e-2, scale_parameter=True), 3, seed=14,
+                               label="tall adafm")
+    assert_ok(errs, label="tall adafm")
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_ragged_rows_leave_their_neighbours_alone(dtype):
     """The last lane of a row reads columns it does not own; only its own are
