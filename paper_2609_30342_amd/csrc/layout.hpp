@@ -39,6 +39,8 @@ constexpr int kRowsPerWave = RK_ROWS_PER_WAVE;  // rows per wave of a matrix til
 constexpr int kChunkRows = kThreads;            // rows per partial sum of R
 constexpr int kSmallSetTiles = 256;             // compute units of the chip
 constexpr int kRaggedVec = 4;                   // elements per lane access of ragged rows
+constexpr int64_t kTinyTiles = 512;             // ragged tiles, and elements of each, of the
+constexpr int64_t kTinyTileElems = 1792;        // planner's rule for one-column tiles instead
 constexpr int64_t kShortLaunch = 8192;          // tiles of a launch bound by tile latency
 constexpr int64_t kShortRagged = 4096;          // the same where some are ragged
 constexpr int kVecIters = 4;                    // vector tile = kThreads*vec*kVecIters

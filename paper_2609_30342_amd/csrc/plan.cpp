@@ -168,15 +168,40 @@ int matrix_blocks(int64_t n, int32_t vec, bool ragged, int base, std::vector<Blo
     int rpw = base << (blog - (lead_llog < blog ? lead_llog : blog));
     return rpw > kMaxRowsPerWave ? kMaxRowsPerWave : rpw;
 }
+
+// Whether the ragged rows of a storage type take one-column tiles instead of
+// 4-wide ones.  A launch of many tiles of a few elements lasts as long as its
+// rounds of workgroups, and a compute unit holds four of the one-column kernel's
+// (58 registers in fp32), two of the 4-wide one's (95).  So: no matrix that
+// needs the 4-wide kernel anyway, more tiles than the 512 it runs at once, less
+// than 1,792 elements in each, and fewer than two one-column tiles for each.
+// R-iKFAD step, fp32, 4-wide / one-column: 3,000 matrices of 3 x 5 27.1 / 16.4 us,
+// 2,000 of 20 x 33 28.5 / 21.5, 1,000 of 64 x 16 16.1 / 12.0 (bf16 15.2 / 11.6);
+// on the other side of the line 500 of 128 x 7 9.2 / 9.3, 1,000 of 64 x 33 19.2 /
+// 24.6 (two tiles for one), 300 of 300 x 9 11.8 / 14.0.
+bool tiny_ragged(const rikfad_tensor *t, int64_t count, int32_t dtype, int rows_per_wave)
+{
+    const int base = rows_per_wave > 0 ? rows_per_wave : kRowsPerWave;
+    int64_t tiles = 0, narrow = 0, elems = 0;
+    std::vector<Block> blocks;
+    for (int64_t i = 0; i < count; ++i) {
+        const rikfad_tensor &T = t[i];
+        if (T.m == 1 || T.n < kRaggedVec || T.dtype != dtype) continue;
+        if (matrix_vec(T) != 1) return false;
+        const int wide_rpw = matrix_blocks(T.n, kRaggedVec, true, base, blocks);
+        tiles += static_cast<int64_t>(blocks.size()) *
+                 ceil_div(T.m, int64_t(kStreamWaves) * wide_rpw);
+        const int rpw = matrix_blocks(T.n, 1, false, base, blocks);
+        narrow += static_cast<int64_t>(blocks.size()) * ceil_div(T.m, int64_t(kStreamWaves) * rpw);
+        elems += T.m * T.n;
+    }
+    return tiles > kTinyTiles && elems < tiles * kTinyTileElems && narrow < 2 * tiles;
+}
 }  // namespace
 
 rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::string &err,
                           int rows_per_wave)
 {
-    // Rows of at least one access; shorter ones stay on the one-column path.
-    auto is_ragged = [](const rikfad_tensor &T) {
-        return T.n >= kRaggedVec && matrix_vec(T) == 1;
-    };
     if (count < 0 || (count > 0 && !t)) {
         err = "tensor list is NULL or count < 0";
         return RIKFAD_EINVAL;
@@ -199,6 +224,14 @@ rikfad_status plan_rikfad(const rikfad_tensor *t, int64_t count, Plan &pl, std::
             return RIKFAD_EALIGN;
         }
     }
+
+    // Rows of at least one access run 4-wide, shorter ones one column a lane;
+    // thousands of tiny tiles of a storage type all stay on the latter.
+    const bool tiny[2] = {tiny_ragged(t, count, RIKFAD_FP32, rows_per_wave),
+                          tiny_ragged(t, count, RIKFAD_BF16, rows_per_wave)};
+    auto is_ragged = [&tiny](const rikfad_tensor &T) {
+        return T.n >= kRaggedVec && matrix_vec(T) == 1 && !tiny[T.dtype == RIKFAD_FP32 ? 0 : 1];
+    };
 
     // A set with fewer matrix tiles than the chip has compute units leaves
     // most of it idle, and its step lasts as long as one tile's chain of

@@ -6,8 +6,48 @@
 #include "plan_check.cpp"
 #undef main
 
+// Ragged tiles of a set of `count` m x n matrices, all of one storage type, and
+// one aligned 8 x 8 matrix of that type if `even`.
+static int ragged_tiles(int count, int64_t m, int64_t n, int32_t dtype, bool even = false)
+{
+    std::vector<rikfad_tensor> ts(static_cast<size_t>(count) + (even ? 1 : 0));
+    for (size_t i = 0; i < ts.size(); ++i) {
+        rikfad_tensor &t = ts[i];
+        const uintptr_t slot = (uintptr_t(1) << 40) + (uintptr_t(i) << 24);
+        const bool last = even && i + 1 == ts.size();
+        t = rikfad_tensor{};
+        t.m = last ? 8 : m;
+        t.n = last ? 8 : n;
+        t.dtype = dtype;
+        t.x = reinterpret_cast<void *>(slot + (last ? 0 : 4));
+        t.g = reinterpret_cast<const void *>(slot + (uintptr_t(1) << 21));
+        t.p = reinterpret_cast<float *>(slot + (uintptr_t(2) << 21));
+        t.r = reinterpret_cast<float *>(slot + (uintptr_t(3) << 21));
+        t.c = reinterpret_cast<float *>(slot + (uintptr_t(4) << 21));
+    }
+    Plan pl;
+    std::string err;
+    CHECK(plan_rikfad(ts.data(), static_cast<int64_t>(ts.size()), pl, err) == RIKFAD_OK, "%s",
+          err.c_str());
+    check_plan(pl, static_cast<int64_t>(ts.size()), /*tiny=*/pl.groups.back().vec == 1);
+    int ragged = 0;
+    for (const Tile &tl : pl.tiles) ragged += tl.ragged;
+    return ragged;
+}
+
 int main()
 {
+    // Thousands of ragged tiles of a few elements take one-column tiles, unless
+    // the 4-wide kernel has to run for another matrix, the tiles fit in one
+    // round, hold more, or would each be two.
+    for (int32_t dt : {RIKFAD_FP32, RIKFAD_BF16}) {
+        CHECK(ragged_tiles(600, 3, 5, dt) == 0 && ragged_tiles(513, 64, 27, dt) == 0, "tiny tiles");
+        CHECK(ragged_tiles(600, 20, 8, dt) == 0, "tiny tiles of misaligned views");
+        CHECK(ragged_tiles(600, 3, 5, dt, true) == 600, "an aligned matrix beside them");
+        CHECK(ragged_tiles(512, 3, 5, dt) == 512, "one round of tiles");
+        CHECK(ragged_tiles(513, 64, 33, dt) == 513, "two one-column tiles for one");
+        CHECK(ragged_tiles(513, 500, 4, dt) == 513, "tiles of 2,000 elements");
+    }
     std::mt19937_64 rng(99);
     const int64_t ns[] = {2, 3, 4, 5, 7, 9, 27, 33, 63, 129, 253, 255, 256, 257, 259, 384, 509, 513,
                           769, 1000, 1025, 4097, 4353, 5003};
