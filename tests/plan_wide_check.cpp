@@ -48,6 +48,22 @@ int main()
         CHECK(ragged_tiles(513, 64, 33, dt) == 513, "two one-column tiles for one");
         CHECK(ragged_tiles(513, 500, 4, dt) == 513, "tiles of 2,000 elements");
     }
+    // Narrow ragged matrices a little taller than a stripe are shared out evenly.
+    for (int64_t m : {192, 300, 384, 448, 600}) {
+        rikfad_tensor t{};
+        t.m = m;
+        t.n = 27;
+        t.x = t.p = t.r = t.c = reinterpret_cast<float *>(uintptr_t(1) << 40);
+        t.g = t.x;
+        std::vector<rikfad_tensor> ts(256, t);      // past the rule for small sets
+        Plan pl;
+        std::string err;
+        CHECK(plan_rikfad(ts.data(), 256, pl, err) == RIKFAD_OK, "%s", err.c_str());
+        const int64_t stripes = (m + 255) / 256, per_wave = ((m + stripes - 1) / stripes + 7) / 8;
+        for (const Tile &tl : pl.tiles)
+            CHECK(tl.ragged && tl.rpw == (per_wave + 7) / 8 * 8 && pl.tensors[0].nrs == stripes,
+                  "%lld x 27: %d rows per wave", (long long)m, tl.rpw);
+    }
     std::mt19937_64 rng(99);
     const int64_t ns[] = {2, 3, 4, 5, 7, 9, 27, 33, 63, 129, 253, 255, 256, 257, 259, 384, 509, 513,
                           769, 1000, 1025, 4097, 4353, 5003};
