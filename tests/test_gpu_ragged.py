@@ -38,12 +38,30 @@ def test_ragged_widths(dtype, offset):
 
 @pytest.mark.parametrize("specs", [
     [S("a", 1030, 4100), S("b", 3, 4353)],                   # 17 and 18 blocks, 4 waves share
-    [S("a", 17000, 40), S("b", 259, 6001, "bf16")],          # 16 waves share 24 blocks
+    [S("a", 17000, 256), S("b", 259, 6001, "bf16")],         # 532 stripes: 16 waves share 24 blocks
 ], ids=["256_threads", "1024_threads"])
 def test_split_row_items(specs):
     log(f"[case] split row items {specs}")
     _, errs = run_parity(specs, synth.HP_FRICTION, 4, seed=8, label="split rows")
     assert_ok(errs, label="split rows")
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_long_launch_with_ragged_tiles(dtype):
+    """More than 4,096 tiles with ragged ones among them: the streaming kernel's
+    other form, and (394 statistics tiles in one tensor) an Adafactor-m update
+    that does not fold the scale."""
+    specs = [S("head", 40, 50257, dtype), S("even", 70, 512, dtype), S("pair", 40, 3, dtype)]
+    specs += [S(f"t{i}", 3 + i % 3, 5 + i % 2, dtype) for i in range(3800)]
+    log(f"[case] long ragged launch {dtype}")
+    _, errs = run_parity(specs, synth.HP_FRICTION, 3, seed=10, label="long ragged")
+    assert_ok(errs, label="long ragged")
+    _, errs = run_parity(specs, synth.HP_FRICTION, 2, seed=11, two_pass=True,
+                         label="long ragged two-pass")
+    assert_ok(errs, label="long ragged two-pass")
+    _, errs = run_adafm_parity(specs, dict(h=1e-2, scale_parameter=True), 3, seed=12,
+                               label="long ragged adafm")
+    assert_ok(errs, label="long ragged adafm")
 
 
 @pytest.mark.parametrize("n", [5, 8])
