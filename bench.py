@@ -30,7 +30,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "stream_kernel_gpt2s_traffic.json"
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for nm in ("kernels.hip", "device.hpp", "layout.hpp", "plan.cpp"):
+    for nm in ("kernels.hip", "device.hpp", "lanes.hpp", "layout.hpp", "plan.cpp"):
         with open(os.path.join(ROOT, "paper_2609_30342_amd", "csrc", nm), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

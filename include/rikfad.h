@@ -66,8 +66,8 @@ typedef enum { RIKFAD_FP32 = 0, RIKFAD_BF16 = 1 } rikfad_dtype;
  * element size.  Matrices with n >= 4 take 4-wide accesses (128-bit, 64-bit
  * for bf16 x and g), aligned to their size where n is a multiple of 4 and x,
  * g, p are 16-byte aligned (fp32), or x, g 8-byte and p 16-byte aligned
- * (bf16), and otherwise at element alignment; matrices of 2 or 3 columns take
- * a one-column path in the same launch. */
+ * (bf16), and otherwise at element alignment; matrices of 2 or 3 columns, and
+ * sets of hundreds of small unaligned ones, take a one-column path. */
 typedef struct {
     void *x;
     const void *g;

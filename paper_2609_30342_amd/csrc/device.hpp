@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lanes.hpp"
 #include "layout.hpp"
 
 namespace rk {
@@ -224,33 +225,6 @@ template <> struct Raw<uint16_t, 1> {
 };
 
 // ---------------------------------------------------------- reductions
-
-// Lane exchanges in the VALU (moves within 16 lanes, swaps of 16 or 32 lanes):
-// a butterfly of __shfl_xor is a chain of LDS-crossbar round trips, six for
-// every row a wave walks.
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-constexpr int kQuadXor1 = 0xb1;     // lane ^ 1 (quad permutation 1 0 3 2)
-constexpr int kQuadXor2 = 0x4e;     // lane ^ 2 (quad permutation 2 3 0 1)
-constexpr int kHalfMirror = 0x141;  // 7 - lane within 8 lanes
-constexpr int kRowMirror = 0x140;   // 15 - lane within 16 lanes
-
-// v plus the value 16 (32) lanes away: swapping the odd 16-lane rows of one
-// copy with the even rows of another (the upper half with the lower) leaves
-// the two addends side by side.
-__device__ __forceinline__ float add_row16(float v)
-{
-    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
-}
-__device__ __forceinline__ float add_half32(float v)
-{
-    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
-}
 
 // Sum over each group of 2^llog consecutive lanes; the same bits in all of
 // them.  The mirrors pair lanes whose halves already agree.

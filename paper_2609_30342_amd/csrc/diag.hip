@@ -10,8 +10,9 @@
 // exactly R = xi 1 and C = xi^T 1: this file computes them from xi directly.
 //
 // Every quantity is a deterministic reduction (fixed partition, fixed
-// order): row sums one wave per row, column sums in row stripes then
-// folded in stripe order, squared norms per workgroup then folded in order.
+// order): row sums in a wave (or the waves of a workgroup that share the row),
+// column sums per workgroup down its rows (row stripes for n > 16384) then
+// folded in their order, squared norms per workgroup then folded in order.
 // sigma_1 comes from power iteration on xi^T xi started at C / |C| (xi >= 0,
 // so the leading singular vectors are non-negative), normalised on the GPU:
 // the column fold also writes per-workgroup squared-norm partials, from
@@ -26,8 +27,17 @@
 
 #include "../../include/rikfad.h"
 #include "kernels.hpp"
+#include "lanes.hpp"
 
 namespace {
+
+using rk::add_half32;
+using rk::add_row16;
+using rk::dpp;
+using rk::kQuadXor1;
+using rk::kQuadXor2;
+using rk::kRor4;
+using rk::kRor8;
 
 constexpr int kT = 256;            // threads per workgroup
 constexpr int kStatChunk = 4096;   // elements per workgroup of the vector statistics
@@ -117,36 +127,8 @@ __global__ __launch_bounds__(kT) void row_reduce_kernel(const float *__restrict_
 
 // ------------------------------------------------- wave-level sums in VALU
 //
-// Sums across a wave by data-parallel primitives (rotations within 16 lanes,
-// half-row swaps between them): a butterfly through __shfl_xor is a chain of
-// LDS-crossbar round trips, which the one-pass kernels cannot hide.
-
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-constexpr int kQuadXor1 = 0xb1;    // lane ^ 1 (quad permutation 1 0 3 2)
-constexpr int kQuadXor2 = 0x4e;    // lane ^ 2 (quad permutation 2 3 0 1)
-constexpr int kRor4 = 0x124, kRor8 = 0x128;
-
-// v plus the value 16 lanes (32 lanes) away: a swap of the odd rows of one
-// copy with the even rows of another leaves the even rows in the first and
-// the odd rows in the second, at both places.
-__device__ __forceinline__ double add_row16(double v)
-{
-    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-__device__ __forceinline__ double add_half32(double v)
-{
-    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
+// A butterfly through __shfl_xor would be a chain of LDS-crossbar round trips,
+// which the one-pass kernels cannot hide.
 
 // Lane 0's value, as a scalar.
 __device__ __forceinline__ double first_lane(double v)
@@ -776,7 +758,9 @@ rikfad_status check_report_args(const float *xi, int64_t m, int64_t n, double ep
 
 // The fewest waves per row whose registers hold it (4 K columns' weights and
 // sums in 128 registers: K <= 4 within a wave), K = 2 where several waves
-// share a row, up to all 16 waves; K = 3 and 4 only where they must.
+// share a row, up to all 16 waves; K = 3 and 4 only where they must.  The error
+// pass, which runs once a report, spills at K = 4 (24 bytes a lane, 76 where 16
+// waves share a row).
 template <int MODE>
 void launch_onepass(const OnePass &a, int nblk, hipStream_t st)
 {

@@ -79,8 +79,10 @@ template <> struct RingDepth<uint16_t> { static constexpr int value = kRingBF16;
 // -> 40.1 us, TinyViT bf16 (2,340) 44.4 -> 43.3, 64 x 1024^2 fp32 (8,192)
 // 220 -> 217, 256 x 512 6.7 -> 5.4; GPT2-S fp32 (15,275 tiles) 403 -> 414, where
 // the staggered start of the other form pays.  Launches with ragged tiles cross
-// over earlier (8 x 3072 x 769 bf16, 3,072 tiles: 60.2 -> 59.6; a set of 6,600:
-// 159 -> 162).
+// over earlier in bf16, long form / LAT by matrices of 3072 x 769: 768 tiles 20.1 /
+// 19.1 us, 3,072 63.8 / 63.1, 4,608 91.3 / 91.8, 5,376 105.1 / 107.0, 7,680 148.1 /
+// 152.4; fp32 gains 1 to 2% up to 7,680 (768 tiles 26.2 / 24.4, 4,608 116.4 /
+// 115.0, 9,216 225.4 / 226.8).  One line for both, at kShortRagged.
 //
 // Ragged rows against the one-column path that such rows took before (4-byte,
 // in bf16 2-byte loads, 64-column blocks): 768 x 50257 and 8 matrices of 769
@@ -355,7 +357,7 @@ __global__ __launch_bounds__(kStreamThreads) void rikfad_stream_kernel(
         return;
     }
     // Tensors whose rows break 16-byte alignment ride along in the same
-    // launch: ragged tiles, or the one-column path for rows of 2 or 3.
+    // launch: ragged tiles, or the one-column path for rows of 2 or 3 columns.
     if (V > 1 && tile.vec == 1)
         stream_matrix<XT, 1, false, LAT>(td, static_cast<const XT *>(g), tile, ws, k, pending, lds);
     else if (RAG && tile.ragged)

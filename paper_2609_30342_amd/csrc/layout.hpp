@@ -41,8 +41,8 @@ constexpr int kSmallSetTiles = 256;             // compute units of the chip
 constexpr int kRaggedVec = 4;                   // elements per lane access of ragged rows
 constexpr int64_t kTinyTiles = 512;             // ragged tiles, and elements of each, of the
 constexpr int64_t kTinyTileElems = 1792;        // planner's rule for one-column tiles instead
-constexpr int64_t kShortLaunch = 8192;          // tiles of a launch bound by tile latency
-constexpr int64_t kShortRagged = 4096;          // the same where some are ragged
+constexpr int64_t kShortLaunch = 8192;          // most tiles of a short launch (kernels.hip,
+constexpr int64_t kShortRagged = 4096;          // stream_matrix); where some are ragged
 constexpr int kVecIters = 4;                    // vector tile = kThreads*vec*kVecIters
 static_assert(kStreamWaves >= 1 && kStreamWaves <= 16, "a workgroup holds at most 16 waves");
 static_assert(kRingF32 >= 1 && kRingBF16 >= 1, "a ring holds at least one row load");

@@ -116,7 +116,7 @@ class Pair:
 def _buffers(specs, wl, checked, seed, device, x_offset):
     """Device parameters (the workload's initial values) and gradient buffers.
     x_offset > 0 places each parameter and gradient that many elements into
-    a larger buffer (misaligned views, scalar path)."""
+    a larger buffer (misaligned views)."""
     xs, gs = [], []
     for i, sp in enumerate(specs):
         dt = torch.bfloat16 if sp.dtype == "bf16" else torch.float32

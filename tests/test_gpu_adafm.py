@@ -108,9 +108,9 @@ def test_edge_shapes(name, specs):
 
 
 # bf16 matrices whose rows allow 8-byte accesses take 4 elements per lane
-# in all three passes, the others the one-column path, in the same launch
-# with the set's vectors; with x_offset = 2 elements (4 bytes) every bf16
-# row loses the 8-byte alignment and every matrix takes the one-column path.
+# in all three passes, the others do so at element alignment (ragged), in the
+# same launch with the set's vectors; with x_offset = 2 elements (4 bytes)
+# every bf16 row loses the 8-byte alignment and every matrix is ragged.
 BF16_WIDTHS = [S("w4a", 200, 776, "bf16"), S("w4", 64, 36, "bf16"), S("w1", 65, 27, "bf16"),
                S("v", 1, 333, "bf16"), S("w4b", 33, 1024, "bf16"), S("f", 70, 96)]
 
@@ -124,7 +124,7 @@ def test_bf16_read_widths(x_offset):
     assert_ok(errs, label="bf16 read widths")
 
 
-def test_misaligned_views_take_scalar_path():
+def test_misaligned_views_take_ragged_path():
     specs = [S("a", 33, 64), S("b", 1, 50), S("c", 20, 20, "bf16")]
     log("[case] adafm misaligned views")
     _, errs = run_adafm_parity(specs, HP, 4, seed=4, x_offset=1, label="misaligned")

@@ -96,7 +96,7 @@ def test_coefficient_limits(name, hp):
 # ------------------------------------------------------- shapes and tails
 
 EDGE = [
-    ("ragged_n27", [S("a", 300, 27)]),                       # n % 4 != 0 -> scalar path
+    ("ragged_n27", [S("a", 300, 27)]),                       # n % 4 != 0 -> ragged rows
     ("wide_ragged", [S("a", 257, 1000)]),                    # 3 full column blocks + 58 lanes
     ("narrow_L16", [S("a", 513, 64)]),                       # 4 rows per load
     ("narrow_L2", [S("a", 70, 8)]),
@@ -155,7 +155,7 @@ def test_random_sets(seed):
 
 
 def test_many_tiny_tensors():
-    """3,000 tensors of 1 to 40 rows and columns (vectors, one-column and
+    """3,000 tensors of 1 to 40 rows and columns (vectors, ragged and
     4-wide matrices, fp32 and bf16) in one context: one launch per storage
     type over thousands of small tiles, against the oracle."""
     rng = np.random.Generator(np.random.PCG64(np.random.SeedSequence([11, 0x7E1])))
@@ -186,7 +186,7 @@ COLUMN_CASES = [
     ("s64_cap_256_threads", [S("a", 9600, 256)], 6),
     ("s256_two_batches", [S("a", 70000, 256), S("b", 1, 256)], 5),
     # 625 stripes: 1024-thread items of 128 stripe lanes x 32 columns, the
-    # last of 8 columns; the one-column-path matrix shares the launch size
+    # last of 8 columns; the ragged matrix shares the launch size
     ("ragged_1024_threads", [S("a", 20000, 1000), S("b", 300, 27)], 4),
 ]
 
@@ -214,7 +214,7 @@ def test_small_set_rows_per_wave_threshold(m, tiles):
     assert_ok(errs, label=f"threshold {m}")
 
 
-def test_misaligned_views_take_scalar_path():
+def test_misaligned_views_take_ragged_path():
     """Parameters and gradients that start one element into their buffers
     (not 16-byte aligned) still match the oracle."""
     specs = [S("a", 64, 128), S("b", 1, 64), S("c", 33, 96, "bf16")]

@@ -64,6 +64,18 @@ def test_long_launch_with_ragged_tiles(dtype):
     assert_ok(errs, label="long ragged adafm")
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_tiny_unaligned_matrices(dtype):
+    """Hundreds of them and nothing else: one-column tiles."""
+    specs = [S(f"t{i}", 3 + i % 20, 5 + 2 * (i % 9), dtype) for i in range(600)]
+    log(f"[case] tiny unaligned {dtype}")
+    _, errs = run_parity(specs, synth.HP_FRICTION, 4, seed=15, label="tiny")
+    assert_ok(errs, label="tiny")
+    _, errs = run_adafm_parity(specs, dict(h=1e-2, scale_parameter=True), 3, seed=16,
+                               label="tiny adafm")
+    assert_ok(errs, label="tiny adafm")
+
+
 @pytest.mark.parametrize("n", [5, 8])
 def test_more_partial_sums_of_r_than_one_round(n):
     """140,000 rows: 547 partial sums of R, past the 512 that the short launch's
